@@ -16,27 +16,32 @@ __host__ __device__ constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c
 constexpr int RUN_MAX = 63;
 
 // OR-dilated receptor occupancy rows of one snapshot, u32 words
-// [k][Z][q][Y]: level k (window 2^k, k = 0 .. log2(RUN_MAX + 1) - 1, the
+// [k][Z][Y][q]: level k (window 2^k, k = 0 .. log2(RUN_MAX + 1) - 1, the
 // levels runs of at most RUN_MAX points read); slice Z = z + M and row
 // Y = y + M for true coordinates z, y in [-M, N + M) (row (y, z) holds
 // receptor row (y mod N, z mod N): the periodic domain of the FFT with M
 // rows continued past each end, so a row index z + t_z or y + t_y of a
-// ligand point within M of the box needs no reducing); word q holds the
-// row's points x in [32 (q - 1), 32 q), taken mod N, for q in [0, RW), so a
-// run starting at x >= -32 reads its words without wrapping; row Y fastest
-// (a wavefront's 64 consecutive rows read one contiguous 256-byte run per
-// word).  The whole table is 4.0 MB at N = 128, about one XCD's L2.
+// ligand point within M of the box needs no reducing); bit x + M of the
+// row's RW words is point x mod N, x in [-M, 32 RW - M), so a run starting
+// at x >= -M reads its words without wrapping.  A row's words lie together:
+// one 12- or 16-byte load brings all that a run needs of it, and 64
+// consecutive rows are 1280 contiguous bytes at N = 128 (a layout with the
+// rows fastest took one load and three cache lines per word).  The whole
+// table is 2.5 MB at N = 128, inside one XCD's 4 MB L2.  PADW words follow
+// it: a run's load may pass the end of the last row (bits that belong to no
+// box-valid translation).
 template <int N>
 struct Dil {
     static constexpr int NW = N / 32;
     static constexpr int M = 8;
     static constexpr int E = N + 2 * M;
-    static constexpr int RW = NW + 4;
+    static constexpr int RW = (E + 31) / 32;
     static constexpr int K = ilog2c(RUN_MAX + 1);
+    static constexpr int PADW = 8;
     static_assert((1 << (K - 1)) <= N, "a level's window must fit in a row");
-    __host__ __device__ static constexpr int64_t words() { return (int64_t)K * E * RW * E; }
+    __host__ __device__ static constexpr int64_t words() { return (int64_t)K * E * E * RW + PADW; }
     __host__ __device__ static constexpr int64_t index(int k, int Z, int q, int Y) {
-        return (((int64_t)k * E + Z) * RW + q) * E + Y;
+        return (((int64_t)k * E + Z) * E + Y) * RW + q;
     }
 };
 

@@ -83,9 +83,15 @@ __global__ __launch_bounds__(NT) void k_rec_dilate(const uint8_t *__restrict__ o
 #pragma unroll
             for (int w = 0; w < NW; ++w) v[w] |= t[w];
         }
+        // word q holds points 32 q - M + j, j = 0 .. 31, mod N
 #pragma unroll
-        for (int q = 0; q < D::RW; ++q) dil[D::index(k, Z, q, Y)] = v[(q + NW - 1) % NW];
+        for (int q = 0; q < D::RW; ++q) {
+            const uint32_t lo = v[(q + NW - 1) % NW], hi = v[q % NW];
+            dil[D::index(k, Z, q, Y)] = (lo >> (32 - D::M)) | (hi << D::M);
+        }
     }
+    if (r == 0)
+        for (int i = 0; i < D::PADW; ++i) dil[D::words() - D::PADW + i] = 0u;
 }
 
 // ------------------------------------------------------------ ligand runs
@@ -132,15 +138,15 @@ __device__ __forceinline__ bool ball_row(const RunAtom &A, int y, int z, long lo
 }
 
 // A run of the clash test as two words: the byte offset of its first table
-// word for a translation of zero, o = 4 Dil<N>::index(k, z + M, (a + 32) / 32,
-// y + M) (the lane adds 4 (t_z RW E + t_y)), and the two window shifts,
-// a mod 32 | ((a + len - 2^k) mod 32) << 8 | (second window one word on) << 16,
-// with 2^k <= len < 2^(k+1).  The planner keeps z, y, a >= -M and the
-// rows and words a translated run reads inside the table.
+// word for a translation of zero, o = 4 Dil<N>::index(k, z + M, b / 32,
+// y + M) with b = a + M (the lane adds 4 RW (t_z E + t_y)), and the two
+// window shifts, b mod 32 | ((b + len - 2^k) mod 32) << 8 | (second window
+// one word on) << 16, with 2^k <= len < 2^(k+1).  The planner keeps z, y,
+// a >= -M and the rows and words a translated run reads inside the table.
 template <int N>
 __device__ __forceinline__ uint2 pack_run(int z, int y, int a, int len) {
     using D = Dil<N>;
-    const int ax = a + 32;
+    const int ax = a + D::M;
     const int k = 31 - __builtin_clz((unsigned)len);
     const int p2 = ax + len - (1 << k);
     const uint32_t off = (uint32_t)(4 * D::index(k, z + D::M, ax >> 5, y + D::M));
@@ -273,23 +279,50 @@ __global__ __launch_bounds__(NT) void k_lig_runs(const CfgDev *__restrict__ cfgs
 // configuration's list, lane = one undecided row (tz, ty), test every run.
 // Only the configurations that still have undecided rows (those near
 // clash-free translations) pay for the full run list.
-constexpr int CLASH_R1 = 96;
+constexpr int CLASH_R1 = 96;      // runs of phase 1
+constexpr int CLASH_CHORDS = 32;  // of these the first so many in order, the others spread
+
+// K consecutive words of a table row, one or two loads
+template <int K>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int vo, int so, uint32_t *v) {
+    static_assert(K >= 3 && K <= 6, "words of a run");
+    if constexpr (K == 3) {
+        const u32x3 t = __builtin_amdgcn_raw_buffer_load_b96(rsrc, vo, so, 0);
+        v[0] = t.x, v[1] = t.y, v[2] = t.z;
+    } else {
+        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, so, 0);
+        v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
+        if constexpr (K == 5) v[4] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, vo + 16, so, 0);
+        if constexpr (K == 6) {
+            const u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(rsrc, vo + 16, so, 0);
+            v[4] = u.x, v[5] = u.y;
+        }
+    }
+}
 
 // Runs k in [k0, k1) of one wavefront: run index k itself (phase 2) or the
 // k-th of the spread sample (phase 1: the first NCH runs, the atom chords,
-// then stride S over the rest).  Lane row (tzl, ty); W output words per
-// lane; UR runs in flight (their table words all requested before use).
-// Runs are at most 63 points long, so a run's second window starts at most
-// one word after its first: the words q1 .. q1 + W + 1 of its row serve both.
-template <int N, int W, bool SAMPLE>
-__device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr, int k1, int NCH, int S, int tzl,
-                                           int ty, bool act, uint32_t lm, __amdgpu_buffer_rsrc_t rsrc,
-                                           uint32_t *acc) {
+// then stride S over the rest).  Lane row
+// (tzl, ty); W output words per lane; UR runs in flight (their table words
+// all requested before use).  Runs are at most 63 points long, so a run's
+// second window starts at most one word after its first: the words q1 ..
+// q1 + W + 1 of its row serve both.  rl, k and the run entries are
+// wave-uniform and must be so for the compiler (derived from blockIdx or
+// readfirstlane): the entries then come by scalar loads and their offset
+// travels in an SGPR.  With an offset the compiler takes for a lane value
+// every table load became a loop over the distinct offsets, 2700 cycles per
+// four runs.  Bound: the loads' way through L1 (16 bytes a lane and run).
+// 8000 site configurations (25 atoms, 96^3 in 128^3): phase 1 4.1 -> 2.0 ms,
+// phase 2 32.0 -> 5.95 ms with uniform entries, whole-row loads and the
+// runs of a row split over four wavefronts.  `share`
+// is called every few groups to exchange acc with the wavefronts that test
+// other runs of the same rows; a wavefront stops once its rows are full.
+template <int N, int W, bool SAMPLE, class Share>
+__device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr, int k0, int k1, int NCH, int S,
+                                           int tzl, int ty, bool act, uint32_t lm,
+                                           __amdgpu_buffer_rsrc_t rsrc, uint32_t *acc, Share &&share) {
     using D = Dil<N>;
-    // runs in flight (their table words all requested before use): few, so
-    // that the kernel's 42 VGPRs let two of its wavefronts sit beside the z
-    // kernel's three on a SIMD when it runs on the second stream
-    constexpr int UR = W <= 1 ? 6 : (W == 2 ? 4 : (W == 3 ? 3 : 2));
+    constexpr int UR = W <= 2 ? 8 : 4;
     // phase 1: position m of the strided walk over the runs after the chords
     int m = 0;
     const int R = nr - NCH;
@@ -300,7 +333,7 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
         if (m >= R) m -= R;
         return i;
     };
-    const int vo = (tzl * (D::RW * D::E) + ty) * 4;  // the lane's part of every table offset
+    const int vo = (tzl * D::E + ty) * (D::RW * 4);  // the lane's part of every table offset
     auto test = [&](auto urc, int k) {
         constexpr int U = decltype(urc)::value;
         uint32_t v[U][W + 2];
@@ -309,9 +342,7 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
         for (int u = 0; u < U; ++u) {
             const uint2 e = rl[run_index(k + u)];
             meta[u] = e.y;
-#pragma unroll
-            for (int j = 0; j < W + 2; ++j)
-                v[u][j] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, vo, (int)e.x + j * (D::E * 4), 0);
+            load_words<W + 2>(rsrc, vo, (int)e.x, v[u]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -331,7 +362,16 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
         for (int w = 0; w < W; ++w) full = full && ((w == W - 1) ? ((acc[w] & lm) == lm) : (acc[w] == ~0u));
         return __all(!act || full) != 0;
     };
-    int k = 0;
+    int k = k0;
+    if (!SAMPLE && k1 - k0 >= UR) {
+        // the last group starts early enough to be whole: a run tested twice is harmless
+        for (int g = 0; k < k1; k += UR, ++g) {
+            test(std::integral_constant<int, UR>{}, min(k, k1 - UR));
+            if ((g & 3) == 3) share(acc);
+            if (all_full()) return;
+        }
+        return;
+    }
     for (; k + UR <= k1; k += UR) {
         test(std::integral_constant<int, UR>{}, k);
         if (all_full()) return;
@@ -339,18 +379,21 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
     for (; k < k1; ++k) test(std::integral_constant<int, 1>{}, k);
 }
 
-template <int N, bool SAMPLE>
-__device__ __forceinline__ void clash_dispatch(int W, const uint2 *rl, int nr, int k1, int NCH, int S, int tzl,
-                                               int ty, bool act, uint32_t lm, __amdgpu_buffer_rsrc_t rsrc,
-                                               uint32_t *acc) {
+template <int N, bool SAMPLE, class Share>
+__device__ __forceinline__ void clash_dispatch(int W, const uint2 *rl, int nr, int k0, int k1, int NCH, int S,
+                                               int tzl, int ty, bool act, uint32_t lm,
+                                               __amdgpu_buffer_rsrc_t rsrc, uint32_t *acc, Share &&share) {
     constexpr int NW = N / 32;
+#define FFTDG_RUNS(WW) \
+    clash_runs<N, WW, SAMPLE>(rl, nr, k0, k1, NCH, S, tzl, ty, act, lm, rsrc, acc, share)
     switch (W) {  // wave-uniform
-    case 1: clash_runs<N, 1, SAMPLE>(rl, nr, k1, NCH, S, tzl, ty, act, lm, rsrc, acc); break;
-    case 2: if constexpr (NW >= 2) clash_runs<N, 2, SAMPLE>(rl, nr, k1, NCH, S, tzl, ty, act, lm, rsrc, acc); break;
-    case 3: if constexpr (NW >= 3) clash_runs<N, 3, SAMPLE>(rl, nr, k1, NCH, S, tzl, ty, act, lm, rsrc, acc); break;
-    case 4: if constexpr (NW >= 4) clash_runs<N, 4, SAMPLE>(rl, nr, k1, NCH, S, tzl, ty, act, lm, rsrc, acc); break;
+    case 1: FFTDG_RUNS(1); break;
+    case 2: if constexpr (NW >= 2) FFTDG_RUNS(2); break;
+    case 3: if constexpr (NW >= 3) FFTDG_RUNS(3); break;
+    case 4: if constexpr (NW >= 4) FFTDG_RUNS(4); break;
     default: break;
     }
+#undef FFTDG_RUNS
 }
 
 // Phase 1.  Free bits (box-valid and clash-free) of a decided row (tz, ty)
@@ -368,7 +411,7 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
                                                 int32_t *__restrict__ scnt) {
     using D = Dil<N>;
     constexpr int NW = D::NW;
-    const int item = (int)blockIdx.x * (NT / 64) + ((int)threadIdx.x >> 6);
+    const int item = (int)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (item >= n_items) return;
     const int lane = threadIdx.x & 63;
     const int ic = find_cfg(item_off, n_cfg, item);
@@ -386,14 +429,14 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     for (int w = 0; w < NW; ++w) acc[w] = 0u;
     const int nr = run_count[ic];
     const int k1 = min(nr, CLASH_R1);
-    const int NCH = min(nr, 32);
+    const int NCH = min(nr, CLASH_CHORDS);
     // stride of the spread sample: near 0.618 of the runs after the chords;
     // with no more runs than phase 1 tests, every one of them in order (a
     // stride sharing a factor with their number would miss some)
     const int S = nr <= CLASH_R1 ? 1 : (nr - NCH) * 618 / 1000;
     const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
-    clash_dispatch<N, true>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, k1, NCH, S, tz, ty, act, lm,
-                            rsrc, acc);
+    clash_dispatch<N, true>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, 0, k1, NCH, S, tz, ty, act, lm,
+                            rsrc, acc, [](uint32_t *) {});
     const bool final = k1 == nr;  // every run tested: the row is decided either way
     bool full = true, any = false;
 #pragma unroll
@@ -424,8 +467,13 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     if (lane == 0) live[c.item_base + loc] = bal != 0ull ? 1 : 0;
 }
 
-// Phase 2: wavefront (configuration, w) takes undecided rows [64 w, 64 w +
-// 64) of the configuration's list and tests every run.
+// Phase 2: block (configuration, w) takes undecided rows [64 w, 64 w + 64) of
+// the configuration's list; its wavefronts test a quarter of the runs each,
+// in interleaved groups, and exchange what they found through LDS.  A row
+// with a free bit has to meet every run (about 1550 at the site), and one
+// wavefront walking them alone was a chain of some 350 us even on an idle
+// chip; a chunk of 256 configurations has about 3000 such wavefronts for the
+// 8192 places the chip has, so the quarters also fill it.
 template <int N>
 __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2_off, int n_cfg, int n_items,
                                                 const CfgDev *__restrict__ cfgs, const uint32_t *__restrict__ runs,
@@ -434,14 +482,14 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
                                                 uint8_t *__restrict__ live, const uint32_t *__restrict__ surv,
                                                 const int32_t *__restrict__ scnt) {
     using D = Dil<N>;
-    constexpr int NW = D::NW;
-    const int item = (int)blockIdx.x * (NT / 64) + ((int)threadIdx.x >> 6);
-    if (item >= n_items) return;
-    const int lane = threadIdx.x & 63;
+    constexpr int NW = D::NW, NWV = NT / 64;
+    __shared__ uint32_t sacc[NW][64];
+    const int item = (int)blockIdx.x;
     const int ic = find_cfg(item2_off, n_cfg, item);
     const int wv = item - item2_off[ic];
     const int cnt = scnt[ic];
-    if (64 * wv >= cnt) return;  // wave-uniform
+    if (64 * wv >= cnt) return;  // block-uniform
+    const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const CfgDev c = cfgs[ic];
     const int Vx = c.V[0], Vy = c.V[1];
     const int ny = (Vy + 63) >> 6;
@@ -454,22 +502,35 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
     uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W;
     uint32_t acc[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) acc[w] = (act && w < W) ? o[w] : 0u;
-    const int nr = run_count[ic];
-    const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
-    clash_dispatch<N, false>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, nr, 0, 1, tz, ty, act, lm,
-                             rsrc, acc);
-    bool any = false;
-    if (act) {
+    for (int w = 0; w < NW; ++w) {
+        acc[w] = (act && w < W) ? o[w] : 0u;
+        if (part == 0) sacc[w][lane] = acc[w];
+    }
+    __syncthreads();
+    // clash bits only ever get set, so wavefronts may exchange them unordered
+    auto share = [&](uint32_t *a) {
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-            if (w < W) {
-                const uint32_t f = ~acc[w] & (w == W - 1 ? lm : ~0u);
-                o[w] = f;
-                any = any || f != 0u;
-            }
-        if (any) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
-    }
+            if (w < W) a[w] |= atomicOr(&sacc[w][lane], a[w]);
+    };
+    const int nr = run_count[ic];
+    const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
+    // this wavefront's quarter of the runs after the chords, which phase 1 tested
+    const int n0 = min(nr, CLASH_CHORDS), nq = nr - n0;
+    clash_dispatch<N, false>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, n0 + nq * part / NWV,
+                             n0 + nq * (part + 1) / NWV, 0, 1, tz, ty, act, lm, rsrc, acc, share);
+    share(acc);
+    __syncthreads();
+    if (part != 0 || !act) return;
+    bool any = false;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        if (w < W) {
+            const uint32_t f = ~sacc[w][lane] & (w == W - 1 ? lm : ~0u);
+            o[w] = f;
+            any = any || f != 0u;
+        }
+    if (any) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
 }
 
 __global__ void k_zero32(int32_t *__restrict__ p, int n) {
@@ -991,8 +1052,8 @@ struct LaunchFused {
         hipLaunchKernelGGL((k_clash1<N>), dim3((n_items + NT / 64 - 1) / (NT / 64)), dim3(NT), 0, st, item_off,
                            n_cfg, n_items, cfgs, runs, run_count, dil, fb, live, surv, scnt);
         if (n_items2 > 0)
-            hipLaunchKernelGGL((k_clash2<N>), dim3((n_items2 + NT / 64 - 1) / (NT / 64)), dim3(NT), 0, st,
-                               item2_off, n_cfg, n_items2, cfgs, runs, run_count, dil, fb, live, surv, scnt);
+            hipLaunchKernelGGL((k_clash2<N>), dim3(n_items2), dim3(NT), 0, st, item2_off, n_cfg, n_items2, cfgs, runs,
+                               run_count, dil, fb, live, surv, scnt);
         return hipGetLastError();
     }
     static int atoms_per_table() {
