@@ -58,30 +58,52 @@ struct FusedSet {
     // chunk: two words per run from runs[2 run_off], run_count[local index]
     hipError_t (*lig_runs)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *ulat,
                            const double *thr, uint32_t *runs, int32_t *run_count);
+    // clears n ints
+    hipError_t (*zero)(hipStream_t, int32_t *p, int64_t n);
     // free bits and live flags: item_off[0..n_cfg] running counts of the
     // phase-1 items (tz, 64-row group), item2_off those of the phase-2 items
     // (64-row slices of a configuration's undecided-row list); surv holds the
-    // lists (at surv_off), scnt their lengths (n_cfg ints, cleared here)
+    // lists (at surv_off), scnt their lengths, fcnt the free translations per
+    // configuration (n_cfg ints each, zero on entry)
     hipError_t (*clash)(hipStream_t, const int32_t *item_off, const int32_t *item2_off, int n_cfg, int n_items,
                         int n_items2, const CfgDev *cfgs, const uint32_t *runs, const int32_t *run_count,
-                        const uint32_t *dil, uint32_t *fb, uint8_t *live, uint32_t *surv, int32_t *scnt);
+                        const uint32_t *dil, uint32_t *fb, uint8_t *live, uint32_t *surv, int32_t *scnt,
+                        int32_t *fcnt);
+    // direct energies: per scanned configuration its atoms' corner offsets
+    // and weights (nz x max_atoms records of corner_bytes); which
+    // configurations go through the transforms (zlist, need, out[2] as
+    // k_modes writes them; done: one int per configuration, zero at the
+    // chunk's start); Eq. 2 plane partials of the others from the receptor
+    // grids [3][n_rec^3]
+    size_t corner_bytes;
+    hipError_t (*corner_atoms)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
+                               const int32_t *ulat, const void *gam, int n_rec, void *atoms);
+    hipError_t (*modes)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *fcnt,
+                        int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out);
+    hipError_t (*direct)(hipStream_t, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
+                         const void *atoms, int max_atoms, const void *grids, int n_rec, double beta,
+                         const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp);
     // per scanned configuration of a chunk: its atoms sorted by plane with
     // their x/y placement and channel weights, and the plane starts
     // (zat: nz x max_atoms records, zbt: nz x (N + 2) ints)
     hipError_t (*zprep)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
                         const int32_t *ulat, const void *gam, void *zat, int32_t *zbt);
     size_t zat_bytes;  // bytes of one atom record
-    // z pass of one snapshot (spectra rspec, 3 energy channels)
+    // z pass of one snapshot (spectra rspec, 3 energy channels); with clash,
+    // of the configurations zlist[0 .. nfft[0]) (indices into zcfg)
     hipError_t (*zpass)(hipStream_t, bool zhalf, bool clash, const CfgDev *cfgs, const int32_t *zcfg, int nz,
                         int max_atoms, const void *zat, const int32_t *zbt, const void *rspec, const void *tw,
-                        void *wsi, const uint8_t *live);
+                        void *wsi, const uint8_t *live, const int32_t *zlist, const int32_t *nfft);
     // z pass of one snapshot from energy planes in ws (direct forward pass)
     hipError_t (*zplanes)(hipStream_t, bool zhalf, bool clash, const CfgDev *cfgs, const int32_t *zcfg, int nz,
-                          const void *ws, const void *rspec, const void *tw, void *wsi, const uint8_t *live);
-    // inverse xy + Eq. 2 plane partials; e_count (nullable) counts planes read
+                          const void *ws, const void *rspec, const void *tw, void *wsi, const uint8_t *live,
+                          const int32_t *zlist, const int32_t *nfft);
+    // inverse xy + Eq. 2 plane partials; e_count (nullable) counts planes read;
+    // fcnt (nullable): only the configurations that go through the transforms
     hipError_t (*inv)(hipStream_t, bool clash, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
                       const void *wsi, double beta, const void *tw, const uint32_t *fb, const uint8_t *live,
-                      void *pp, void *psi_out, uint8_t *clash_out, unsigned int *e_count);
+                      void *pp, void *psi_out, uint8_t *clash_out, unsigned int *e_count, const int32_t *fcnt,
+                      const int32_t *nfft);
     // dynamic LDS bytes of the z kernel for ligands of up to max_atoms atoms
     size_t (*z_lds)(int max_atoms);
 };

@@ -396,19 +396,28 @@ __device__ __forceinline__ void clash_dispatch(int W, const uint2 *rl, int nr, i
 #undef FFTDG_RUNS
 }
 
+// Adds the lanes' counts to *total.
+__device__ __forceinline__ void wave_count(int n, int lane, int32_t *total) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+    if (lane == 0 && n) atomicAdd(total, n);
+}
+
 // Phase 1.  Free bits (box-valid and clash-free) of a decided row (tz, ty)
 // go to fb[free_off + (tz Vy + ty) W + w], W = ceil(Vx / 32), bit tx & 31 of
 // word tx >> 5; an undecided row leaves its clash bits so far there and is
 // appended to the list at surv_off as (tz << 16 | ty), scnt[local config]
 // counting.  live[item_base + tz ny + g] = 1 iff the group has a free bit
-// once decided (0 until phase 2 decides its undecided rows).
+// once decided (0 until phase 2 decides its undecided rows).  fcnt[local
+// config] counts the free translations of both phases (scnt and fcnt start
+// at zero).
 template <int N>
 __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_off, int n_cfg, int n_items,
                                                 const CfgDev *__restrict__ cfgs, const uint32_t *__restrict__ runs,
                                                 const int32_t *__restrict__ run_count,
                                                 const uint32_t *__restrict__ dil, uint32_t *__restrict__ fb,
                                                 uint8_t *__restrict__ live, uint32_t *__restrict__ surv,
-                                                int32_t *__restrict__ scnt) {
+                                                int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt) {
     using D = Dil<N>;
     constexpr int NW = D::NW;
     const int item = (int)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -447,6 +456,7 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
             const uint32_t f = ~acc[w] & (w == W - 1 ? lm : ~0u);
             full = full && f == 0u;
         }
+    int nfree = 0;
     if (act) {
         uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W;
 #pragma unroll
@@ -455,6 +465,7 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
                 const uint32_t f = ~acc[w] & (w == W - 1 ? lm : ~0u);
                 o[w] = (final || full) ? f : acc[w];
                 any = any || f != 0u;
+                nfree += __popc(f);
             }
     }
     const bool und = act && !full && !final;
@@ -467,6 +478,7 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     }
     const unsigned long long bal = __ballot(final && any);
     if (lane == 0) live[c.item_base + loc] = bal != 0ull ? 1 : 0;
+    if (bal) wave_count(nfree, lane, fcnt + ic);
 }
 
 // Phase 2: block (configuration, w) takes undecided rows [64 w, 64 w + 64) of
@@ -482,7 +494,7 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
                                                 const int32_t *__restrict__ run_count,
                                                 const uint32_t *__restrict__ dil, uint32_t *__restrict__ fb,
                                                 uint8_t *__restrict__ live, const uint32_t *__restrict__ surv,
-                                                const int32_t *__restrict__ scnt) {
+                                                const int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt) {
     using D = Dil<N>;
     constexpr int NW = D::NW, NWV = NT / 64;
     __shared__ uint32_t sacc[NW][64];
@@ -523,21 +535,233 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
                              n0 + nq * (part + 1) / NWV, 0, 1, tz, ty, act, lm, rsrc, acc, share);
     share(acc);
     __syncthreads();
-    if (part != 0 || !act) return;
-    bool any = false;
+    if (part != 0) return;
+    int nfree = 0;
+    if (act) {
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-        if (w < W) {
-            const uint32_t f = ~sacc[w][lane] & (w == W - 1 ? lm : ~0u);
-            o[w] = f;
-            any = any || f != 0u;
-        }
-    if (any) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
+        for (int w = 0; w < NW; ++w)
+            if (w < W) {
+                const uint32_t f = ~sacc[w][lane] & (w == W - 1 ? lm : ~0u);
+                o[w] = f;
+                nfree += __popc(f);
+            }
+        if (nfree) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
+    }
+    wave_count(nfree, lane, fcnt + ic);
 }
 
 __global__ void k_zero32(int32_t *__restrict__ p, int n) {
     const int i = (int)blockIdx.x * NT + (int)threadIdx.x;
     if (i < n) p[i] = 0;
+}
+
+// ------------------------------------------------------------ direct energies
+// Eq. 8 with the trilinear weights written out: at translation t,
+//   Psi(t) = sum_a sum_(8 corners) w sum_ch gamma_ch G_ch(floor(u_a) + t + corner),
+// the sum the transforms evaluate at every translation.  Where few
+// translations are clash-free it is evaluated at those alone (k_direct): no
+// forward planes, no z pass, no inverse.  What decides is the number of
+// (free translation, atom) pairs of a configuration and snapshot, known on
+// the device once the clash test is done; a configuration with more than
+// direct_pairs goes through the transforms, listed by k_modes.  The lines lie
+// where the two cost the same (one stream, us per configuration): N = 128,
+// FP32: 7.3 ns per 1000 pairs (347 k pairs: 2.5 us) against 7.1-8.4 us of
+// transforms; N = 64: 12 ns per 1000 pairs against 1.15 us in FP32, 13 ns
+// against 2.3 us in FP64; N = 32: some 13 ns against 0.27 and 0.43 us.
+// 8000 site configurations (25 atoms, 3 % of the translations free, 160 k
+// pairs each): 46.0 ms of forward planes, z pass and inverse -> 6.9 ms.
+template <typename T, int N>
+__host__ __device__ constexpr long long direct_pairs() {
+    return N == 128 ? 1000000 : (N == 64 ? (sizeof(T) == 8 ? 150000 : 100000) : (sizeof(T) == 8 ? 30000 : 20000));
+}
+template <typename T, int N>
+__device__ __forceinline__ bool by_transforms(int n_free, int n_atoms) {
+    return (long long)n_free * n_atoms > direct_pairs<T, N>();
+}
+
+// A placed atom of a scanned configuration as k_direct reads it (by scalar
+// loads): byte offset of its first corner in one channel's grid, and the
+// weight of corner (dz, dy, dx) for channel ch at [(2 dz + dy) 6 + 2 ch + dx].
+template <typename T>
+struct alignas(16) CornerAtom {
+    int32_t off;
+    int32_t pad[3];
+    T w[24];
+};
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_corner_atoms(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg,
+                                                     int nz, int ma, const int32_t *__restrict__ ulat,
+                                                     const T *__restrict__ gam, int n_rec,
+                                                     CornerAtom<T> *__restrict__ out) {
+    const int e = (int)blockIdx.x * NT + (int)threadIdx.x;
+    const int zi = e / ma, a = e - (e / ma) * ma;
+    if (zi >= nz) return;
+    const CfgDev c = cfgs[zcfg[zi]];
+    if (a >= c.n_atoms) return;
+    const int32_t *U = ulat + 3 * (c.u_base + a);
+    double f[3][2];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        f[d][1] = (double)(U[d] & 0xffff) * (1.0 / 65536.0);
+        f[d][0] = 1.0 - f[d][1];
+    }
+    CornerAtom<T> r;
+    r.off = (((U[2] >> 16) * n_rec + (U[1] >> 16)) * n_rec + (U[0] >> 16)) * (int)sizeof(T);
+    r.pad[0] = r.pad[1] = r.pad[2] = 0;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+        const double g = (double)gam[3 * (c.atom_base + a) + ch];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)  // k = 4 dz + 2 dy + dx; rounded once
+            r.w[(k >> 1) * 6 + 2 * ch + (k & 1)] = (T)(f[2][k >> 2] * f[1][(k >> 1) & 1] * f[0][k & 1] * g);
+    }
+    out[(int64_t)zi * ma + a] = r;
+}
+
+// The configurations of one (chunk, snapshot) that go through the transforms:
+// zlist[0 .. out[0]) their indices among the scanned ones, in order;
+// need[local] = 1 for those whose forward planes are not there yet (out[1]
+// of them), noted in done.  One block.
+template <typename T, int N>
+__global__ __launch_bounds__(NT) void k_modes(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg, int nz,
+                                              const int32_t *__restrict__ fcnt, int32_t *__restrict__ done,
+                                              int32_t *__restrict__ zlist, uint8_t *__restrict__ need,
+                                              int32_t *__restrict__ out) {
+    __shared__ int sh[NT / 64];
+    int base = 0, nneed = 0, total;
+    for (int z0 = 0; z0 < nz; z0 += NT) {
+        const int zi = z0 + (int)threadIdx.x;
+        int l = 0;
+        bool fft = false, nd = false;
+        if (zi < nz) {
+            l = zcfg[zi];
+            fft = by_transforms<T, N>(fcnt[l], cfgs[l].n_atoms);
+            nd = fft && done[l] == 0;
+            need[l] = nd ? 1 : 0;
+            if (nd) done[l] = 1;
+        }
+        const int pos = base + block_excl_scan(fft ? 1 : 0, total, sh);
+        if (fft) zlist[pos] = zi;
+        base += total;
+        nneed += __syncthreads_count(nd);
+    }
+    if (threadIdx.x == 0) {
+        out[0] = base;
+        out[1] = nneed;
+    }
+}
+
+// One block per (configuration, box-valid z-translation): the plane's free
+// translations, in order of their linear index, one per thread; a wavefront
+// walks the configuration's atoms, whose corners come as 12 loads of an
+// x-adjacent pair (3 channels x 4 rows) at the lane's translation plus an
+// offset in an SGPR, and whose 24 weights are scalar operands.  Bound: the
+// loads' way through L1 (96 bytes per pair of translation and atom).
+template <int N>
+__host__ __device__ constexpr int direct_threads() {
+    return N == 128 ? 256 : 64;
+}
+template <typename T, int N>
+__global__ __launch_bounds__(direct_threads<N>()) void k_direct(
+    const int32_t *__restrict__ inv_off, int n_cfg, const CfgDev *__restrict__ cfgs,
+    const CornerAtom<T> *__restrict__ atoms, int ma, const T *__restrict__ grids, int n_rec, T beta,
+    const uint32_t *__restrict__ fb, const uint8_t *__restrict__ live, const int32_t *__restrict__ fcnt,
+    PlanePartial<T> *__restrict__ pp) {
+    constexpr int ND = direct_threads<N>(), NW = N / 32;
+    constexpr int MAXW = N * NW;                   // words of a plane's free bits
+    constexpr int PER = (MAXW + ND - 1) / ND;
+    using T2 = typename Cx<T>::t;
+    __shared__ int pre[PER * ND + 1];              // free translations before each word
+    __shared__ int sh[ND / 64];
+    __shared__ LseAcc<T> red[ND / 64];
+    const int ic = find_cfg(inv_off, n_cfg, (int)blockIdx.x);
+    const CfgDev &c = cfgs[ic];
+    const int n_atoms = c.n_atoms;
+    if (by_transforms<T, N>(fcnt[ic], n_atoms)) return;
+    const int Vx = c.V[0], Vy = c.V[1], tz = (int)blockIdx.x - inv_off[ic];
+    LseAcc<T> acc;
+    acc.init();
+    const int ny = (Vy + 63) >> 6;
+    bool l = false;
+    for (int g = 0; g < ny; ++g) l = l || live[c.item_base + tz * ny + g] != 0;
+    if (!l) {  // block-uniform: every translation of the plane clashes
+        if (threadIdx.x == 0) {
+            PlanePartial<T> o;
+            o.m = -(T)INFINITY;
+            o.s = (T)0;
+            o.psi_min = (T)INFINITY;
+            o.n_finite = 0;
+            o.argmin = -1;
+            pp[c.pp_base + tz] = o;
+        }
+        return;
+    }
+    const int W = (Vx + 31) >> 5, nw = Vy * W;
+    const uint32_t *fp = fb + c.free_off + (int64_t)tz * nw;
+    // running counts over the plane's words: thread t owns words PER t ..
+    int cnt[PER], mine = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int w = PER * (int)threadIdx.x + k;
+        cnt[k] = w < nw ? __popc(fp[w]) : 0;
+        mine += cnt[k];
+    }
+    int x = mine;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) sh[wv] = x;
+    __syncthreads();
+    int base = x - mine, F = 0;
+#pragma unroll
+    for (int i = 0; i < ND / 64; ++i) {
+        base += i < wv ? sh[i] : 0;
+        F += sh[i];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        pre[PER * threadIdx.x + k] = base;
+        base += cnt[k];
+    }
+    __syncthreads();
+    const int row = n_rec * (int)sizeof(T), plane = n_rec * row;
+    const int chan = n_rec * plane;
+    const auto rs = make_rsrc(grids, 3 * chan);
+    const CornerAtom<T> *__restrict__ A = atoms + (int64_t)c.zrow * ma;
+    for (int j = threadIdx.x; j < F; j += ND) {
+        // word holding free translation j, then its (j - pre)-th set bit
+        int lo = 0, hi = nw;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= j) lo = mid; else hi = mid;
+        }
+        uint32_t b = fp[lo];
+        for (int k = j - pre[lo]; k > 0; --k) b &= b - 1u;
+        const int ty = lo / W, tx = 32 * (lo - (lo / W) * W) + __builtin_ctz(b);
+        const int vo = ((tz * n_rec + ty) * n_rec + tx) * (int)sizeof(T);
+        double sum = 0.0;  // over atoms in FP64: two instructions beside an atom's 24
+#pragma unroll 2
+        for (int a = 0; a < n_atoms; ++a) {
+            const int off = A[a].off;
+            T e[2] = {(T)0, (T)0};
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) {
+                    const T2 v = buf_load(rs, vo, off + ch * chan + (p >> 1) * plane + (p & 1) * row, (T2 *)nullptr);
+                    e[0] += A[a].w[6 * p + 2 * ch] * v.x;
+                    e[1] += A[a].w[6 * p + 2 * ch + 1] * v.y;
+                }
+            sum += (double)(e[0] + e[1]);
+        }
+        const T psi = (T)sum;
+        acc.add(-beta * psi, psi, (tz * Vy + ty) * Vx + tx);
+    }
+    block_partial_store<T, ND>(acc, red, pp + c.pp_base + tz);
 }
 
 // ------------------------------------------------------------ z pass
@@ -598,19 +822,50 @@ __global__ __launch_bounds__(NT) void k_zprep(const CfgDev *__restrict__ cfgs, c
 }
 
 // Block -> (tile of P z-pencils, configuration), with the XCD-aware order
-// of the plane path's z kernel.  ZHI: the configuration's energy window
+// of the plane path's z kernel: block b of a launch of nb takes logical index
+// (b mod 8) (nb / 8) + b / 8.  LIST: the configurations are those of zlist,
+// nfft[0] of them, a count the host does not know; a grid of fixed size
+// then strides over the same order (a launch that finds no configuration
+// ends after one load a block).
+template <bool LIST>
+struct ZWork {
+    int nz, total, nb, b;
+    const int32_t *zlist;
+    __device__ ZWork(int n, int n_tiles, const int32_t *list, const int32_t *nfft) {
+        nz = LIST ? nfft[0] : n;
+        total = n_tiles * nz;
+        nb = LIST ? (total + 7) & ~7 : (int)gridDim.x;
+        b = (int)blockIdx.x;
+        zlist = list;
+    }
+    __device__ bool more() const { return b < nb; }
+    __device__ void next() { b = LIST ? b + (int)gridDim.x : nb; }
+    __device__ bool at(int &tile, int &zi) const {
+        const int L = (nb % 8 == 0) ? (b % 8) * (nb / 8) + b / 8 : b;
+        if (L >= total) return false;
+        tile = L / nz;
+        zi = L - tile * nz;
+        if (LIST) zi = zlist[zi];
+        return true;
+    }
+};
+
+// ZHI: the configuration's energy window
 // (L_e planes, loaded from plane 0; the correlation of the shifted grid is
 // the wanted one shifted by ze0, undone at the store) fits in the lower half
 // of the pencil, so the first radix-2 stage is pruned.  CLASH: store only
 // the z-translations whose live flag is set; a configuration with none is
 // skipped whole.
+// (The 128-point FP32 instantiations are held to 3 waves per SIMD.)
 template <typename T, int N, bool ZHI, bool CLASH>
-__global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg,
+__global__ __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu((N == 128 && sizeof(T) == 4) ? 3 : 1))) void k_zfused(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg,
                                                 int nz, int n_tiles, int ma, int ac,
                                                 const ZAtom<T> *__restrict__ zat, const int32_t *__restrict__ zbt,
                                                 const typename Cx<T>::t *__restrict__ rspec,
                                                 const typename Cx<T>::t *__restrict__ twg,
-                                                typename Cx<T>::t *__restrict__ wsi, const uint8_t *__restrict__ live) {
+                                                typename Cx<T>::t *__restrict__ wsi, const uint8_t *__restrict__ live,
+                                                const int32_t *__restrict__ zlist, const int32_t *__restrict__ nfft) {
     using C2 = typename Cx<T>::t;
     using G = Geo<T, N>;
     constexpr int R1 = G::R1, R2 = G::R2, P = G::U, NP = G::NP, H = G::H, PW = G::PW, PAD = G::PAD;
@@ -622,30 +877,32 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
     __shared__ int4 pd[N];        // plane j: atoms [x, z) of plane j - 1 (to y) and of plane j
     __shared__ uint32_t smask[R1];  // bit i: FFT lane n1 stores its output slot i
     extern __shared__ __align__(16) unsigned char dyn[];
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int L = (nb % 8 == 0) ? (b % 8) * (nb / 8) + b / 8 : b;
-    if (L >= n_tiles * nz) return;
-    const int tile = L / nz, zi = L % nz;
+    ZWork<CLASH> work(nz, n_tiles, zlist, nfft);
+    if (!CLASH || work.more()) load_tw<T, N>(tw, twg);
+    for (; work.more(); work.next()) {
+    int tile, zi;
+    if (!work.at(tile, zi)) continue;
+    const int tid = CLASH ? opaque(threadIdx.x) : (int)threadIdx.x;  // nothing held across items
     const CfgDev c = cfgs[zcfg[zi]];
     const int Vz = c.V[2];
-    if (threadIdx.x < N / 32) lv[threadIdx.x] = 0u;
+    if (tid < N / 32) lv[tid] = 0u;
     __syncthreads();
     if (CLASH) {
         const int ny = (c.V[1] + 63) >> 6;
-        for (int tz = threadIdx.x; tz < Vz; tz += NT) {
+        for (int tz = tid; tz < Vz; tz += NT) {
             bool l = false;
             for (int g = 0; g < ny; ++g) l = l || live[c.item_base + tz * ny + g] != 0;
             if (l) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
         }
     } else {
-        for (int tz = threadIdx.x; tz < Vz; tz += NT) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
+        for (int tz = tid; tz < Vz; tz += NT) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
     }
     __syncthreads();
     {
         uint32_t any = 0u;
 #pragma unroll
         for (int w = 0; w < N / 32; ++w) any |= lv[w];
-        if (any == 0u) return;  // block-uniform: no translation of this configuration is clash-free
+        if (any == 0u) continue;  // block-uniform: no translation of this configuration is clash-free
     }
     // dynamic LDS (ma = most atoms of a ligand in the launch): per sorted
     // atom its x/y placement, its channel weights [ch][corner][atom], then
@@ -655,8 +912,7 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
     T *sfr = (T *)(((uintptr_t)(sxy + ma) + 15) & ~(uintptr_t)15);           // [ma][2] fx, fy
     T *swt = sfr + 2 * ma;                                                    // [6][ma]
     C2 *F = (C2 *)(((uintptr_t)(swt + 6 * ma) + 15) & ~(uintptr_t)15);       // [ac][FP]
-    load_tw<T, N>(tw, twg);
-    for (int a = threadIdx.x; a < n; a += NT) {
+    for (int a = tid; a < n; a += NT) {
         const ZAtom<T> A = zat[(int64_t)zi * ma + a];
         sxy[a] = make_int2(A.ax, A.ay);
         sfr[2 * a] = A.fx;
@@ -664,22 +920,22 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
 #pragma unroll
         for (int k = 0; k < 6; ++k) swt[k * ma + a] = A.w[k];  // k = corner * 3 + ch: (1 - fz) for 0..2, fz for 3..5
     }
-    for (int j = threadIdx.x; j < c.Le; j += NT) {
+    for (int j = tid; j < c.Le; j += NT) {
         const int32_t *zr = zbt + (int64_t)zi * (N + 2) + j;
         pd[j] = make_int4(zr[0], zr[1], zr[2], 0);
     }
-    if (threadIdx.x < R1) {
+    if (tid < R1) {
         // FFT lane n1 holds output z = n1 + R1 i, translation (z - ze0) mod N
         uint32_t m = 0u;
 #pragma unroll
         for (int i = 0; i < R2; ++i) {
-            const int tt = ((int)threadIdx.x + R1 * i - c.ze0) & (N - 1);
+            const int tt = (tid + R1 * i - c.ze0) & (N - 1);
             m |= (uint32_t)(tt < Vz && ((lv[tt >> 5] >> (tt & 31)) & 1u)) << i;
         }
-        smask[threadIdx.x] = m;
+        smask[tid] = m;
     }
     __syncthreads();
-    const ZLane<N> zl;
+    const ZLane<N> zl(tid);
     const int n1 = zl.n1, p = zl.p;
     C2 *ex = buf + zl.w * G::WREG + zl.pl;
     const int nchunk = (n + ac - 1) / ac;
@@ -688,12 +944,12 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
     const int rlane = rs_lane<T, N>(n1, ok ? pen : 0);
     auto build_table = [&](int e0) {
         const int na = min(ac, n - e0);
-        const int q = (int)threadIdx.x % P;
+        const int q = tid % P;
         const int pq = tile * P + q;
         const bool okq = pq < NP;
         const int kyq = okq ? pq / H : 0, kxq = okq ? pq - (pq / H) * H : 0;
         const C2 wx = tw[kxq & (N - 1)], wy = tw[kyq & (N - 1)];
-        for (int e = (int)threadIdx.x / P; e < na; e += NT / P) {
+        for (int e = tid / P; e < na; e += NT / P) {
             const int2 axy = sxy[e0 + e];
             const T fx = sfr[2 * (e0 + e)], fy = sfr[2 * (e0 + e) + 1];
             const C2 ex_ = tw[(kxq * axy.x) & (N - 1)], ey = tw[(kyq * axy.y) & (N - 1)];
@@ -712,7 +968,7 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
     // (free until the transform), element j of pencil pl at
     // j PW + (j / R2) PAD + pl; each lane then reads its slots.
     C2 *wbuf = buf + zl.w * G::WREG;
-    const int lane = threadIdx.x & 63;
+    const int lane = tid & 63;
     const int fcol = zl.w * PW;  // first table column of this wavefront's pencils
     constexpr int NIN = ZHI ? R2 / 2 : R2;
 #pragma unroll 1
@@ -774,6 +1030,8 @@ __global__ __launch_bounds__(NT) void k_zfused(const CfgDev *__restrict__ cfgs, 
         const int tt = (n1 + R1 * i - c.ze0) & (N - 1);
         buf_store(rd, ((sm >> i) & 1u) ? (tt * NP + pen) * (int)sizeof(C2) : oor, C2{er[i], ei[i]});
     }
+    if (CLASH) __syncthreads();  // the next item reuses the block's tables
+    }
 }
 
 // z pass from energy planes in device memory (the direct per-atom x/y DFT of
@@ -786,7 +1044,8 @@ __global__ __launch_bounds__(NT) void k_zplanes(const CfgDev *__restrict__ cfgs,
                                                  int nz, int n_tiles, const typename Cx<T>::t *__restrict__ ws,
                                                  const typename Cx<T>::t *__restrict__ rspec,
                                                  const typename Cx<T>::t *__restrict__ twg,
-                                                 typename Cx<T>::t *__restrict__ wsi, const uint8_t *__restrict__ live) {
+                                                 typename Cx<T>::t *__restrict__ wsi, const uint8_t *__restrict__ live,
+                                                 const int32_t *__restrict__ zlist, const int32_t *__restrict__ nfft) {
     using C2 = typename Cx<T>::t;
     using G = Geo<T, N>;
     constexpr int R1 = G::R1, R2 = G::R2, P = G::U, NP = G::NP, PW = G::PW, PAD = G::PAD;
@@ -795,43 +1054,44 @@ __global__ __launch_bounds__(NT) void k_zplanes(const CfgDev *__restrict__ cfgs,
     __shared__ C2 tw[N];
     __shared__ uint32_t lv[N / 32];
     __shared__ uint32_t smask[R1];  // bit i: FFT lane n1 stores its output slot i
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int L = (nb % 8 == 0) ? (b % 8) * (nb / 8) + b / 8 : b;
-    if (L >= n_tiles * nz) return;
-    const int tile = L / nz, zi = L % nz;
+    ZWork<CLASH> work(nz, n_tiles, zlist, nfft);
+    if (!CLASH || work.more()) load_tw<T, N>(tw, twg);
+    for (; work.more(); work.next()) {
+    int tile, zi;
+    if (!work.at(tile, zi)) continue;
+    const int tid = CLASH ? opaque(threadIdx.x) : (int)threadIdx.x;  // nothing held across items
     const CfgDev c = cfgs[zcfg[zi]];
     const int Vz = c.V[2];
-    if (threadIdx.x < N / 32) lv[threadIdx.x] = 0u;
+    if (tid < N / 32) lv[tid] = 0u;
     __syncthreads();
     if (CLASH) {
         const int ny = (c.V[1] + 63) >> 6;
-        for (int tz = threadIdx.x; tz < Vz; tz += NT) {
+        for (int tz = tid; tz < Vz; tz += NT) {
             bool l = false;
             for (int g = 0; g < ny; ++g) l = l || live[c.item_base + tz * ny + g] != 0;
             if (l) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
         }
     } else {
-        for (int tz = threadIdx.x; tz < Vz; tz += NT) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
+        for (int tz = tid; tz < Vz; tz += NT) atomicOr(&lv[tz >> 5], 1u << (tz & 31));
     }
     __syncthreads();
     {
         uint32_t any = 0u;
 #pragma unroll
         for (int w = 0; w < N / 32; ++w) any |= lv[w];
-        if (any == 0u) return;  // block-uniform: no translation of this configuration is clash-free
+        if (any == 0u) continue;  // block-uniform: no translation of this configuration is clash-free
     }
-    load_tw<T, N>(tw, twg);
-    if (threadIdx.x < R1) {
+    if (tid < R1) {
         uint32_t m = 0u;
 #pragma unroll
         for (int i = 0; i < R2; ++i) {
-            const int tt = ((int)threadIdx.x + R1 * i - c.ze0) & (N - 1);
+            const int tt = (tid + R1 * i - c.ze0) & (N - 1);
             m |= (uint32_t)(tt < Vz && ((lv[tt >> 5] >> (tt & 31)) & 1u)) << i;
         }
-        smask[threadIdx.x] = m;
+        smask[tid] = m;
     }
     __syncthreads();
-    const ZLane<N> zl;
+    const ZLane<N> zl(tid);
     const int n1 = zl.n1, p = zl.p;
     C2 *ex = buf + zl.w * G::WREG + zl.pl;
     const int pen = tile * P + p;
@@ -870,6 +1130,8 @@ __global__ __launch_bounds__(NT) void k_zplanes(const CfgDev *__restrict__ cfgs,
         const int tt = (n1 + R1 * i - c.ze0) & (N - 1);
         buf_store(rd, ((sm >> i) & 1u) ? (tt * NP + pen) * (int)sizeof(C2) : oor, C2{er[i], ei[i]});
     }
+    if (CLASH) __syncthreads();  // the next item reuses the block's tables
+    }
 }
 
 // ------------------------------------------------------------ inverse xy
@@ -877,13 +1139,15 @@ __global__ __launch_bounds__(NT) void k_zplanes(const CfgDev *__restrict__ cfgs,
 // packed columns, C2R along x on row pairs, Eq. 2 partial over the
 // clash-free translations.  CLASH: free bits from k_clash; a plane without
 // any is not read (its partial is empty) unless energies are exported.
+// LIST: only the configurations that go through the transforms (nfft[0] of
+// them; k_direct has the others), by a grid that strides over the items.
 // WT threads per plane (N = 128: 512, 64 units with one packed column and
 // one row pair each, two planes per CU at 4 wavefronts per SIMD).
 template <int N>
 __host__ __device__ constexpr int inv_fused_threads() {
     return N == 128 ? 512 : NT;
 }
-template <typename T, int N, bool CLASH, int WT = inv_fused_threads<N>()>
+template <typename T, int N, bool CLASH, bool LIST, int WT = inv_fused_threads<N>()>
 __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32_t *__restrict__ inv_off, int n_cfg,
                                                    const CfgDev *__restrict__ cfgs,
                                                    const typename Cx<T>::t *__restrict__ wsi, T beta, T inv_n3,
@@ -891,7 +1155,9 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
                                                    const uint32_t *__restrict__ fb, const uint8_t *__restrict__ live,
                                                    PlanePartial<T> *__restrict__ pp, T *__restrict__ psi_out,
                                                    uint8_t *__restrict__ clash_out,
-                                                   unsigned int *__restrict__ e_count) {
+                                                   unsigned int *__restrict__ e_count, int n_items,
+                                                   const int32_t *__restrict__ fcnt,
+                                                   const int32_t *__restrict__ nfft) {
     using C2 = typename Cx<T>::t;
     using G = Geo<T, N>;
     constexpr int R1 = G::R1, R2 = G::R2, M = G::M, S = G::S, U = WT / R1, NP = G::NP;
@@ -900,9 +1166,14 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
     __shared__ C2 Pl[N * S];
     __shared__ C2 tw[N];
     __shared__ LseAcc<T> red[WT / 64];
-    const int ic = find_cfg(inv_off, n_cfg, (int)blockIdx.x);
+    if (LIST && nfft[0] == 0) return;
+    load_tw<T, N>(tw, twg);
+    for (int item = (int)blockIdx.x; item < n_items; item = LIST ? item + (int)gridDim.x : n_items) {
+    const int ic = find_cfg(inv_off, n_cfg, item);
     const CfgDev c = cfgs[ic];
-    const int Vx = c.V[0], Vy = c.V[1], tz = (int)blockIdx.x - inv_off[ic];
+    if (LIST && !by_transforms<T, N>(fcnt[ic], c.n_atoms)) continue;
+    const int tid = LIST ? opaque(threadIdx.x) : (int)threadIdx.x;  // nothing held across items
+    const int Vx = c.V[0], Vy = c.V[1], tz = item - inv_off[ic];
     const bool exporting = psi_out != nullptr || clash_out != nullptr;
     LseAcc<T> acc;
     acc.init();
@@ -911,7 +1182,7 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
         bool l = false;
         for (int g = 0; g < ny; ++g) l = l || live[c.item_base + tz * ny + g] != 0;
         if (!l) {  // block-uniform: every translation of the plane clashes
-            if (threadIdx.x == 0) {
+            if (tid == 0) {
                 PlanePartial<T> o;
                 o.m = -(T)INFINITY;
                 o.s = (T)0;
@@ -920,14 +1191,13 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
                 o.argmin = -1;
                 pp[c.pp_base + tz] = o;
             }
-            return;
+            continue;
         }
     }
-    if (threadIdx.x == 0 && e_count) atomicAdd(e_count, 1u);
-    load_tw<T, N>(tw, twg);
-    const int unit = threadIdx.x / R1, n1 = threadIdx.x % R1;
+    if (tid == 0 && e_count) atomicAdd(e_count, 1u);
+    const int unit = tid / R1, n1 = tid % R1;
     const C2 *src = wsi + c.off_inv + (int64_t)tz * NP;
-    plane_copy<T, N, true, WT>(Pl, const_cast<C2 *>(src));
+    plane_copy<T, N, true, WT>(Pl, const_cast<C2 *>(src), tid);
     __syncthreads();
     T re[R2], im[R2];
     // inverse y on columns (kx = 0 and N/2 packed into column 0), keep y < Vy
@@ -973,6 +1243,7 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
     // inverse x (C2R) of row pairs (y, y+1), y < Vy
     const int npairs = (Vy + 1) / 2;
     const int rounds_a = (npairs + U - 1) / U;
+    const int m1 = LIST ? opaque(n1) & (R1 - 1) : n1;
     for (int rd = 0; rd < rounds_a; ++rd) {
         const int y = 2 * (unit + U * rd);
         const bool lv = y < Vy;
@@ -993,7 +1264,7 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
         C2 *row = Pl + (lv ? y * S : 0);
 #pragma unroll
         for (int i = 0; i < R2; ++i) {
-            const int k = n1 + R1 * i;
+            const int k = m1 + R1 * i;
             re[i] = im[i] = (T)0;
             if (lv) {
                 // row values at k (k <= N/2) or conj at N - k; kx = 0, N/2 are real
@@ -1006,32 +1277,37 @@ __global__ __launch_bounds__(WT, WT == 512 ? 4 : 1) void k_inv_fused(const int32
                 im[i] = a.y + bq.x;
             }
         }
-        fft_unit<T, N, true>(re, im, n1, row, 1, tw, lv, G::RPAD);
+        fft_unit<T, N, true>(re, im, m1, row, 1, tw, lv, G::RPAD);
         if (lv) {
             // clash flags in the epilogue's slot layout: bit 2 sl + h is
-            // (x, y + h) with x = spec_index(n1, sl / R1, sl % R1)
+            // (x, y + h) with x = spec_index(m1, sl / R1, sl % R1)
             uint32_t cb = 0u;
             if (CLASH) {
 #pragma unroll
                 for (int sl = 0; sl < R2; ++sl) {
                     const int k1 = sl % R1;
-                    const int x = spec_index<N>(n1, sl / R1, k1);
+                    const int x = spec_index<N>(m1, sl / R1, k1);
                     const int wi = (R2 * k1) >> 5;  // x >> 5 (compile-time)
                     cb |= (uint32_t)(((f0[wi] >> (x & 31)) & 1u) == 0u) << (2 * sl);
                     cb |= (uint32_t)(((f1[wi] >> (x & 31)) & 1u) == 0u) << (2 * sl + 1);
                 }
             }
             uint32_t vb;
-            (void)row_pair_epilogue<T, N, CLASH>(re, im, n1, y, Vx, Vy, tz, false, cb, inv_n3, beta, psi_out,
+            (void)row_pair_epilogue<T, N, CLASH>(re, im, m1, y, Vx, Vy, tz, false, cb, inv_n3, beta, psi_out,
                                                 clash_out, acc, vb);
         }
     }
-    block_partial_store<T, WT>(acc, red, pp + c.pp_base + tz);
+    block_partial_store<T, WT>(acc, red, pp + c.pp_base + tz, tid);
+    }
 }
 
 // ------------------------------------------------------------ launchers
 template <typename T, int N>
 struct LaunchFused {
+    // blocks of a launch over a list made on the device: a few times what the
+    // chip holds of them (z pass three, inverse two a compute unit), so that the
+    // last round is short and an empty list costs about 5 us
+    static constexpr int LIST_BLOCKS_Z = 3072, LIST_BLOCKS = 1024;
     using C2 = typename Cx<T>::t;
     using G = Geo<T, N>;
     static hipError_t rec_dilate(hipStream_t st, const uint8_t *occ, int n_rec, uint32_t *dil) {
@@ -1045,17 +1321,42 @@ struct LaunchFused {
         hipLaunchKernelGGL((k_lig_runs<N>), dim3(nz), dim3(NT), 0, st, cfgs, zcfg, ulat, thr, runs, run_count);
         return hipGetLastError();
     }
+    static hipError_t zero(hipStream_t st, int32_t *p, int64_t n) {
+        if (n <= 0) return hipSuccess;
+        hipLaunchKernelGGL(k_zero32, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, st, p, (int)n);
+        return hipGetLastError();
+    }
     static hipError_t clash(hipStream_t st, const int32_t *item_off, const int32_t *item2_off, int n_cfg,
                             int n_items, int n_items2, const CfgDev *cfgs, const uint32_t *runs,
                             const int32_t *run_count, const uint32_t *dil, uint32_t *fb, uint8_t *live,
-                            uint32_t *surv, int32_t *scnt) {
+                            uint32_t *surv, int32_t *scnt, int32_t *fcnt) {
         if (n_items <= 0) return hipSuccess;
-        hipLaunchKernelGGL(k_zero32, dim3((n_cfg + NT - 1) / NT), dim3(NT), 0, st, scnt, n_cfg);
         hipLaunchKernelGGL((k_clash1<N>), dim3((n_items + NT / 64 - 1) / (NT / 64)), dim3(NT), 0, st, item_off,
-                           n_cfg, n_items, cfgs, runs, run_count, dil, fb, live, surv, scnt);
+                           n_cfg, n_items, cfgs, runs, run_count, dil, fb, live, surv, scnt, fcnt);
         if (n_items2 > 0)
             hipLaunchKernelGGL((k_clash2<N>), dim3(n_items2), dim3(NT), 0, st, item2_off, n_cfg, n_items2, cfgs, runs,
-                               run_count, dil, fb, live, surv, scnt);
+                               run_count, dil, fb, live, surv, scnt, fcnt);
+        return hipGetLastError();
+    }
+    static hipError_t corner_atoms(hipStream_t st, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
+                                   const int32_t *ulat, const void *gam, int n_rec, void *atoms) {
+        if (nz <= 0) return hipSuccess;
+        hipLaunchKernelGGL((k_corner_atoms<T>), dim3((unsigned)(((int64_t)nz * max_atoms + NT - 1) / NT)), dim3(NT), 0,
+                           st, cfgs, zcfg, nz, max_atoms, ulat, (const T *)gam, n_rec, (CornerAtom<T> *)atoms);
+        return hipGetLastError();
+    }
+    static hipError_t modes(hipStream_t st, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *fcnt,
+                            int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out) {
+        hipLaunchKernelGGL((k_modes<T, N>), dim3(1), dim3(NT), 0, st, cfgs, zcfg, nz, fcnt, done, zlist, need, out);
+        return hipGetLastError();
+    }
+    static hipError_t direct(hipStream_t st, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
+                             const void *atoms, int max_atoms, const void *grids, int n_rec, double beta,
+                             const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp) {
+        if (n_items <= 0) return hipSuccess;
+        hipLaunchKernelGGL((k_direct<T, N>), dim3(n_items), dim3(direct_threads<N>()), 0, st, inv_off, n_cfg, cfgs,
+                           (const CornerAtom<T> *)atoms, max_atoms, (const T *)grids, n_rec, (T)beta, fb, live, fcnt,
+                           (PlanePartial<T> *)pp);
         return hipGetLastError();
     }
     static int atoms_per_table() {
@@ -1078,18 +1379,24 @@ struct LaunchFused {
                            max_atoms, ulat, (const T *)gam, (ZAtom<T> *)zat, zbt);
         return hipGetLastError();
     }
+    // blocks of a z pass: one per (tile, configuration), or, over a list whose
+    // length only the device knows, as many as keep the chip full
+    static long long z_blocks(int n_tiles, int nz, bool list) {
+        const long long nb = ((long long)n_tiles * nz + 7) / 8 * 8;
+        return list && nb > LIST_BLOCKS_Z ? LIST_BLOCKS_Z : nb;
+    }
     static hipError_t zpass(hipStream_t st, bool zhalf, bool clash, const CfgDev *cfgs, const int32_t *zcfg, int nz,
                             int max_atoms, const void *zat, const int32_t *zbt, const void *rspec, const void *tw,
-                            void *wsi, const uint8_t *live) {
+                            void *wsi, const uint8_t *live, const int32_t *zlist, const int32_t *nfft) {
         if (nz <= 0) return hipSuccess;
         const int n_tiles = (G::NP + G::U - 1) / G::U;
-        long long nb = (long long)n_tiles * nz;
-        nb = (nb + 7) / 8 * 8;
+        const long long nb = z_blocks(n_tiles, nz, clash);
         const int ac = max_atoms < atoms_per_table() ? max_atoms : atoms_per_table();
         const size_t dyn = dyn_bytes(max_atoms);
 #define FFTDG_ZF(Z, C)                                                                                            \
     hipLaunchKernelGGL((k_zfused<T, N, Z, C>), dim3((unsigned)nb), dim3(NT), dyn, st, cfgs, zcfg, nz, n_tiles,      \
-                       max_atoms, ac, (const ZAtom<T> *)zat, zbt, (const C2 *)rspec, (const C2 *)tw, (C2 *)wsi, live)
+                       max_atoms, ac, (const ZAtom<T> *)zat, zbt, (const C2 *)rspec, (const C2 *)tw, (C2 *)wsi, live, zlist, \
+                       nfft)
         if (zhalf && clash) FFTDG_ZF(true, true);
         else if (zhalf) FFTDG_ZF(true, false);
         else if (clash) FFTDG_ZF(false, true);
@@ -1099,14 +1406,13 @@ struct LaunchFused {
     }
     static hipError_t zplanes(hipStream_t st, bool zhalf, bool clash, const CfgDev *cfgs, const int32_t *zcfg,
                               int nz, const void *ws, const void *rspec, const void *tw, void *wsi,
-                              const uint8_t *live) {
+                              const uint8_t *live, const int32_t *zlist, const int32_t *nfft) {
         if (nz <= 0) return hipSuccess;
         const int n_tiles = (G::NP + G::U - 1) / G::U;
-        long long nb = (long long)n_tiles * nz;
-        nb = (nb + 7) / 8 * 8;
+        const long long nb = z_blocks(n_tiles, nz, clash);
 #define FFTDG_ZP(Z, C)                                                                                     \
     hipLaunchKernelGGL((k_zplanes<T, N, Z, C>), dim3((unsigned)nb), dim3(NT), 0, st, cfgs, zcfg, nz, n_tiles, \
-                       (const C2 *)ws, (const C2 *)rspec, (const C2 *)tw, (C2 *)wsi, live)
+                       (const C2 *)ws, (const C2 *)rspec, (const C2 *)tw, (C2 *)wsi, live, zlist, nfft)
         if (zhalf && clash) FFTDG_ZP(true, true);
         else if (zhalf) FFTDG_ZP(true, false);
         else if (clash) FFTDG_ZP(false, true);
@@ -1116,19 +1422,19 @@ struct LaunchFused {
     }
     static hipError_t inv(hipStream_t st, bool clash, const int32_t *inv_off, int n_cfg, int n_items,
                           const CfgDev *cfgs, const void *wsi, double beta, const void *tw, const uint32_t *fb,
-                          const uint8_t *live, void *pp, void *psi_out, uint8_t *clash_out, unsigned int *e_count) {
+                          const uint8_t *live, void *pp, void *psi_out, uint8_t *clash_out, unsigned int *e_count,
+                          const int32_t *fcnt, const int32_t *nfft) {
         if (n_items <= 0) return hipSuccess;
         const T b = (T)beta, s = (T)(1.0 / ((double)N * N * N));
-        if (clash)
-            hipLaunchKernelGGL((k_inv_fused<T, N, true>), dim3(n_items), dim3(inv_fused_threads<N>()), 0, st, inv_off,
-                               n_cfg, cfgs,
-                               (const C2 *)wsi, b, s, (const C2 *)tw, fb, live, (PlanePartial<T> *)pp, (T *)psi_out,
-                               clash_out, e_count);
-        else
-            hipLaunchKernelGGL((k_inv_fused<T, N, false>), dim3(n_items), dim3(inv_fused_threads<N>()), 0, st, inv_off,
-                               n_cfg, cfgs,
-                               (const C2 *)wsi, b, s, (const C2 *)tw, fb, live, (PlanePartial<T> *)pp, (T *)psi_out,
-                               clash_out, e_count);
+        const int nb = fcnt && n_items > LIST_BLOCKS ? LIST_BLOCKS : n_items;
+#define FFTDG_INV(C, L)                                                                                            \
+    hipLaunchKernelGGL((k_inv_fused<T, N, C, L>), dim3(nb), dim3(inv_fused_threads<N>()), 0, st, inv_off, n_cfg, cfgs, \
+                       (const C2 *)wsi, b, s, (const C2 *)tw, fb, live, (PlanePartial<T> *)pp, (T *)psi_out,        \
+                       clash_out, e_count, n_items, fcnt, nfft)
+        if (clash && fcnt) FFTDG_INV(true, true);
+        else if (clash) FFTDG_INV(true, false);
+        else FFTDG_INV(false, false);
+#undef FFTDG_INV
         return hipGetLastError();
     }
 };
@@ -1141,7 +1447,12 @@ static const FusedSet *make_fused() {
         Dil<N>::M,
         LaunchFused<T, N>::rec_dilate,
         LaunchFused<T, N>::lig_runs,
+        LaunchFused<T, N>::zero,
         LaunchFused<T, N>::clash,
+        sizeof(CornerAtom<T>),
+        LaunchFused<T, N>::corner_atoms,
+        LaunchFused<T, N>::modes,
+        LaunchFused<T, N>::direct,
         LaunchFused<T, N>::zprep,
         sizeof(ZAtom<T>),
         LaunchFused<T, N>::zpass,

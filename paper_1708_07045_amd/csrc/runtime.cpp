@@ -90,7 +90,10 @@ struct fftdg_ctx {
     DevBuf tw, rspec, rxy, ws_fwd, ws_inv, pp, tables, red_B, red_res, red_off, red_W;
     DevBuf dil, runs, run_cnt, fbits, lives;  // fused path: receptor bit rows, ligand runs, clash results
     DevBuf zat, zbt;                          // fused path: sorted atoms and plane starts per configuration
-    DevBuf surv, scnt;                        // fused path: undecided rows of the clash test and their counts
+    DevBuf surv;                              // fused path: undecided rows of the clash test
+    DevBuf counts;                            // fused path: per-item counts of the clash test (see run_plan)
+    DevBuf corners, zlist, need;              // fused path: direct energies' atoms; configurations that take the transforms
+    DevBuf rgrid;                             // receptor grids [snap][3][n_rec^3] of the direct energies (fused path, OCC)
     DevBuf sir_psi, sir_clash, sir_u, sir_lin, sir_psi_out;  // pose resampling
     int n_snap = 0;
     std::vector<double> W;
@@ -555,6 +558,7 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
                 d.free_off = (int32_t)nfw;
                 d.item_base = nit;
                 d.surv_off = (int32_t)nsv;
+                d.zrow = (int32_t)(P.zcfg.size() - ch.z0);
                 P.fwd_off.push_back(nf);
                 P.inv_off.push_back(ni);
                 P.item_off.push_back(nit);
@@ -770,7 +774,32 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         if ((rc = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets))) return rc;
         if ((rc = reserve(ctx, ctx->lives, e_items * nsets))) return rc;
         if ((rc = reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets))) return rc;
-        if ((rc = reserve(ctx, ctx->scnt, sizeof(int32_t) * e_cfgs * nsets))) return rc;
+    }
+    const int s_begin = snap_only >= 0 ? snap_only : 0;
+    const int s_end = snap_only >= 0 ? snap_only + 1 : ctx->n_snap;
+    // hybrid: energies summed directly at the clash-free translations where
+    // they are few, through the transforms otherwise, decided on the device
+    // per configuration and snapshot.  Its counts start at zero, one clear for
+    // the whole scan: per chunk [done: nloc], then per item (chunk, snapshot)
+    // [scnt: nloc][fcnt: nloc][out: 2] with nloc the chunk's configurations.
+    const bool exporting = psi_out != nullptr || clash_out != nullptr;
+    const bool hybrid = P.fused && occ && !exporting;
+    int64_t n_counts = 0, nzmax = 1;
+    std::vector<int64_t> count_off;  // of each chunk
+    if (P.fused && occ) {
+        for (const Plan::Chunk &ch : P.chunks) {
+            const int64_t nloc = ch.c1 - ch.c0;
+            count_off.push_back(n_counts);
+            n_counts += nloc + (int64_t)(s_end - s_begin) * (2 * nloc + 2);
+            nzmax = std::max<int64_t>(nzmax, (int64_t)ch.nz);
+        }
+        if (n_counts > INT32_MAX) return set_err(ctx, FFTDG_E_INVALID, "scan: more than 2^31 clash-test counters in one batch");
+        if ((rc = reserve(ctx, ctx->counts, sizeof(int32_t) * (size_t)n_counts))) return rc;
+    }
+    if (hybrid) {
+        if ((rc = reserve(ctx, ctx->corners, ctx->fs->corner_bytes * (size_t)max_nz_atoms))) return rc;
+        if ((rc = reserve(ctx, ctx->zlist, sizeof(int32_t) * (size_t)nzmax * nsets))) return rc;
+        if ((rc = reserve(ctx, ctx->need, e_cfgs * nsets))) return rc;
     }
     if (overlap && !ctx->side) {
         // the events first: the stream is set only once all of them exist,
@@ -784,8 +813,6 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     }
     // snapshots whose inverse planes share the workspace: the z kernel keeps
     // a configuration's forward spectra in registers across the group
-    const int s_begin = snap_only >= 0 ? snap_only : 0;
-    const int s_end = snap_only >= 0 ? snap_only + 1 : ctx->n_snap;
     const int64_t inv1 = std::max<int64_t>(P.max_inv, 1);
     const int64_t room = (int64_t)(ctx->ws_limit / cb) - P.max_fwd;
     const int grp = P.fused ? 1
@@ -818,10 +845,11 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     // per-chunk data from the device tables, so a captured sequence stays
     // valid for any later scan with the same signature (launch shapes,
     // table layout, buffers, temperature).
-    const bool exporting = psi_out != nullptr || clash_out != nullptr;
     // Fused path: ligand occupancy runs once per chunk; per snapshot the
-    // clash test on bits, the z pass (energy channels, inputs from per-atom
-    // factors) and the inverse xy on the planes holding a clash-free
+    // clash test on bits, then the energies at the clash-free translations:
+    // summed directly, or, for the configurations with many of them, by the
+    // forward planes (first snapshot that needs them), the z pass (energy
+    // channels) and the inverse xy on the planes holding a clash-free
     // translation.
     auto launch_fused = [&](hipStream_t st) -> int {
     const FusedSet *fs = ctx->fs;
@@ -832,7 +860,9 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     auto fb_of = [&](int p) { return (uint32_t *)ctx->fbits.p + (size_t)p * e_free; };
     auto lv_of = [&](int p) { return (uint8_t *)ctx->lives.p + (size_t)p * e_items; };
     auto surv_of = [&](int p) { return (uint32_t *)ctx->surv.p + (size_t)p * e_surv; };
-    auto scnt_of = [&](int p) { return (int32_t *)ctx->scnt.p + (size_t)p * e_cfgs; };
+    auto zlist_of = [&](int p) { return (int32_t *)ctx->zlist.p + (size_t)p * nzmax; };
+    auto need_of = [&](int p) { return (uint8_t *)ctx->need.p + (size_t)p * e_cfgs; };
+    const size_t n3 = (size_t)g.n_rec * g.n_rec * g.n_rec;
     // stream of the occupancy runs and the clash test; with the overlap it
     // starts after the work already ordered on `st` (the table upload)
     hipStream_t sc = st;
@@ -841,21 +871,28 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         HIPCHK(ctx, hipEventRecord(ctx->ev_fork, st));
         HIPCHK(ctx, hipStreamWaitEvent(sc, ctx->ev_fork, 0));
     }
+    if (occ) HIPCHK(ctx, fs->zero(sc, (int32_t *)ctx->counts.p, n_counts));
     int item = 0;
     for (const Plan::Chunk &ch : P.chunks) {
         const CfgDev *ccfg = dcfg + ch.c0;
         const int nloc = ch.c1 - ch.c0;
+        int32_t *done = occ ? (int32_t *)ctx->counts.p + count_off[&ch - P.chunks.data()] : nullptr;
         // the runs of this chunk follow the previous chunk's clash tests on `sc`
         if (occ)
             HIPCHK(ctx, timed(ctx, FFTDG_K_RUNS, 8.0 * (double)ch.nruns, [&] {
                        return fs->lig_runs(sc, ccfg, dz + ch.z0, (int)ch.nz, du, dthr, runs, rcnt);
                    }));
-        if (P.fused_planes)
+        if (hybrid)
+            HIPCHK(ctx, timed(ctx, FFTDG_K_RUNS, (double)ch.nz * ch.max_atoms * fs->corner_bytes, [&] {
+                       return fs->corner_atoms(st, ccfg, dz + ch.z0, (int)ch.nz, std::max(ch.max_atoms, 1), du, dgam,
+                                               g.n_rec, ctx->corners.p);
+                   }));
+        if (P.fused_planes && !hybrid)
             HIPCHK(ctx, timed(ctx, FFTDG_K_FWD, (double)ch.ws_fwd * cb, [&] {
                        return ks->fwd(st, true, dfwd + ch.off0, nloc, (int)ch.nfwd, ccfg, du, dgam, dthr, ctx->tw.p,
                                       ctx->ws_fwd.p);
                    }));
-        else
+        else if (!P.fused_planes)
             HIPCHK(ctx, timed(ctx, FFTDG_K_RUNS, (double)ch.nz * ch.max_atoms * fs->zat_bytes, [&] {
                        return fs->zprep(st, ccfg, dz + ch.z0, (int)ch.nz, std::max(ch.max_atoms, 1), du, dgam,
                                         ctx->zat.p, (int32_t *)ctx->zbt.p);
@@ -864,34 +901,57 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
             const int p = overlap ? (item & 1) : 0;
             uint32_t *fb = fb_of(p);
             uint8_t *lv = lv_of(p);
+            int32_t *scnt = occ ? done + nloc + (size_t)(s - s_begin) * (2 * nloc + 2) : nullptr;
+            int32_t *fcnt = occ ? scnt + nloc : nullptr, *mode = occ ? fcnt + nloc : nullptr;
             if (occ) {
                 // set p was last read by the inverse of item - 2
                 if (overlap && item >= 2) HIPCHK(ctx, hipStreamWaitEvent(sc, ctx->ev_main[p], 0));
                 const uint32_t *dil = (const uint32_t *)ctx->dil.p + (size_t)s * (size_t)fs->dil_words;
                 HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, 4.0 * (double)ch.nfree + (double)ch.nitems, [&] {
                            return fs->clash(sc, ditem + ch.off0, ditem2 + ch.off0, nloc, ch.nitems, ch.nitems2, ccfg,
-                                            runs, rcnt, dil, fb, lv, surv_of(p), scnt_of(p));
+                                            runs, rcnt, dil, fb, lv, surv_of(p), scnt, fcnt);
                        }));
+                if (hybrid)
+                    HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, 4.0 * (double)ch.nz, [&] {
+                               return fs->modes(sc, ccfg, dz + ch.z0, (int)ch.nz, fcnt, done, zlist_of(p), need_of(p),
+                                                mode);
+                           }));
                 if (overlap) {
                     HIPCHK(ctx, hipEventRecord(ctx->ev_side[p], sc));
                     HIPCHK(ctx, hipStreamWaitEvent(st, ctx->ev_side[p], 0));
                 }
             }
             const char *rs = (const char *)ctx->rspec.p + spec_per_snap * s;
-            // planes written are counted on the device (those the inverse reads)
-            HIPCHK(ctx, timed(ctx, FFTDG_K_ZPROD, b_spec3 + (P.fused_planes ? (double)ch.ws_fwd * cb : 0.0), [&] {
-                       if (P.fused_planes)
-                           return fs->zplanes(st, ch.zhalf != 0, occ && !exporting, ccfg, dz + ch.z0, (int)ch.nz,
-                                              ctx->ws_fwd.p, rs, ctx->tw.p, ctx->ws_inv.p, lv);
-                       return fs->zpass(st, ch.zhalf != 0, occ && !exporting, ccfg, dz + ch.z0, (int)ch.nz,
-                                        std::max(ch.max_atoms, 1), ctx->zat.p, (const int32_t *)ctx->zbt.p, rs,
-                                        ctx->tw.p, ctx->ws_inv.p, lv);
-                   }));
             void *pp_s = (char *)ctx->pp.p + pp_snap * (size_t)(s - s_begin);
-            HIPCHK(ctx, timed(ctx, FFTDG_K_INV, pb * ch.pp, [&] {
+            if (hybrid) {
+                HIPCHK(ctx, timed(ctx, FFTDG_K_INV, 3.0 * (double)(n3 * tsz) + 4.0 * (double)ch.nfree + pb * ch.pp, [&] {
+                           return fs->direct(st, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->corners.p,
+                                             std::max(ch.max_atoms, 1), (const char *)ctx->rgrid.p + 3 * n3 * tsz * s,
+                                             g.n_rec, beta, fb, lv, fcnt, pp_s);
+                       }));
+                if (P.fused_planes)
+                    HIPCHK(ctx, timed(ctx, FFTDG_K_FWD, 0.0, [&] {
+                               return ks->fwd_need(st, dfwd + ch.off0, nloc, (int)ch.nfwd, ccfg, du, dgam, ctx->tw.p,
+                                                   ctx->ws_fwd.p, need_of(p), mode + 1);
+                           }));
+            }
+            // planes written are counted on the device (those the inverse reads);
+            // in a hybrid scan these are all of the z pass's and the inverse's bytes
+            const double b_z = hybrid ? 0.0 : b_spec3 + (P.fused_planes ? (double)ch.ws_fwd * cb : 0.0);
+            HIPCHK(ctx, timed(ctx, FFTDG_K_ZPROD, b_z, [&] {
+                       if (P.fused_planes)
+                           return fs->zplanes(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                                              ctx->ws_fwd.p, rs, ctx->tw.p, ctx->ws_inv.p, lv,
+                                              hybrid ? zlist_of(p) : nullptr, mode);
+                       return fs->zpass(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                                        std::max(ch.max_atoms, 1), ctx->zat.p, (const int32_t *)ctx->zbt.p, rs,
+                                        ctx->tw.p, ctx->ws_inv.p, lv, hybrid ? zlist_of(p) : nullptr, mode);
+                   }));
+            HIPCHK(ctx, timed(ctx, FFTDG_K_INV, hybrid ? 0.0 : pb * ch.pp, [&] {
                        return fs->inv(st, occ, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->ws_inv.p, beta,
                                       ctx->tw.p, fb, lv, pp_s, psi_out, clash_out,
-                                      ctx->prof ? (unsigned int *)ctx->prof_cnt.p : nullptr);
+                                      ctx->prof ? (unsigned int *)ctx->prof_cnt.p : nullptr, hybrid ? fcnt : nullptr,
+                                      mode);
                    }));
             if (overlap) HIPCHK(ctx, hipEventRecord(ctx->ev_main[p], st));
             if (ctx->prof) ctx->prof_fused = true;
@@ -984,7 +1044,9 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
                                 (int64_t)(intptr_t)ctx->fbits.p, (int64_t)(intptr_t)ctx->lives.p,
                                 (int64_t)(intptr_t)ctx->dil.p, (int64_t)o_item, (int64_t)(intptr_t)ctx->zat.p,
                                 (int64_t)(intptr_t)ctx->zbt.p, (int64_t)(intptr_t)ctx->surv.p,
-                                (int64_t)(intptr_t)ctx->scnt.p, (int64_t)o_item2,
+                                (int64_t)(intptr_t)ctx->counts.p, (int64_t)o_item2,
+                                (int64_t)(intptr_t)ctx->corners.p, (int64_t)(intptr_t)ctx->zlist.p,
+                                (int64_t)(intptr_t)ctx->need.p, (int64_t)(intptr_t)ctx->rgrid.p,
                                 (int64_t)(intptr_t)out, (int64_t)(intptr_t)ctx->tables.p,
                                 (int64_t)(intptr_t)ctx->ws_fwd.p, (int64_t)(intptr_t)ctx->ws_inv.p,
                                 (int64_t)(intptr_t)ctx->pp.p, (int64_t)(intptr_t)ctx->rspec.p,
@@ -1173,7 +1235,7 @@ void fftdg_destroy(fftdg_ctx *c) {
                       &c->red_B, &c->red_res, &c->red_off, &c->red_W, &c->prof_cnt, &c->tune_out,
                       &c->sir_psi, &c->sir_clash, &c->sir_u, &c->sir_lin, &c->sir_psi_out,
                       &c->dil, &c->runs, &c->run_cnt, &c->fbits, &c->lives, &c->zat, &c->zbt, &c->surv,
-                      &c->scnt};
+                      &c->counts, &c->corners, &c->zlist, &c->need, &c->rgrid};
     for (DevBuf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->pinned) (void)hipHostFree(c->pinned);
@@ -1255,6 +1317,9 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
             HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, (double)n3 + 4.0 * (double)dw, [&] {
                        return ctx->fs->rec_dilate(ctx->stream, occ + s * n3, g.n_rec, (uint32_t *)ctx->dil.p + s * dw);
                    }));
+        // the grids themselves, for the energies summed directly
+        if ((rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
+        HIPCHK(ctx, hipMemcpyAsync(ctx->rgrid.p, grids, 3 * n3 * tsz * n_snap, hipMemcpyDeviceToDevice, ctx->stream));
     }
     ctx->n_snap = n_snap;
     ctx->W = W;

@@ -56,15 +56,23 @@ struct Geo {
     static constexpr int WREG = N * PW + R1 * PAD;
 };
 
+// A copy of v the compiler cannot see through: index arithmetic derived from
+// it is recomputed where it is used instead of being hoisted out of loops and
+// held in registers across the whole kernel.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Lane layout of the z-pencil kernels: wave w, lane l -> pencil w*PW + l%PW
 // of the tile, FFT lane n1 = l / PW.
 template <int N>
 struct ZLane {
     int w, n1, pl, p;
-    __device__ ZLane() {
+    __device__ ZLane(int tid = threadIdx.x) {
         constexpr int PW = 64 / Shape<N>::R1;
-        w = threadIdx.x >> 6;
-        const int l = threadIdx.x & 63;
+        w = tid >> 6;
+        const int l = tid & 63;
         n1 = l / PW;
         pl = l - n1 * PW;
         p = w * PW + pl;
@@ -154,7 +162,7 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int off, dou
 // aligned for FP32 (planes start at multiples of NP, which is even).  NTH
 // threads take part.
 template <typename T, int N, bool TO_LDS, int NTH = NT>
-__device__ __forceinline__ void plane_copy(typename Cx<T>::t *Pl, typename Cx<T>::t *g) {
+__device__ __forceinline__ void plane_copy(typename Cx<T>::t *Pl, typename Cx<T>::t *g, int tid = threadIdx.x) {
     using C2 = typename Cx<T>::t;
     constexpr int H = N / 2 + 1, S = Geo<T, N>::S, NP = N * H;
     constexpr int NPAIR = NP / 2;
@@ -166,17 +174,17 @@ __device__ __forceinline__ void plane_copy(typename Cx<T>::t *Pl, typename Cx<T>
     if (TO_LDS) {
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const int q = threadIdx.x + j * NTH;
+            const int q = tid + j * NTH;
             if (q < NPAIR) v[j] = reinterpret_cast<const Pair *>(g)[q];
         }
     }
-    // (row, column) of element 2q, q = threadIdx.x + j NTH, stepped by 2 NTH
+    // (row, column) of element 2q, q = tid + j NTH, stepped by 2 NTH
     // elements per j instead of divided out per element
     constexpr int DY = (2 * NTH) / H, DX = (2 * NTH) % H;
-    int y0 = (2 * (int)threadIdx.x) / H, x0 = 2 * (int)threadIdx.x - y0 * H;
+    int y0 = (2 * tid) / H, x0 = 2 * tid - y0 * H;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int q = threadIdx.x + j * NTH;
+        const int q = tid + j * NTH;
         if (q < NPAIR) {
             const bool wrap = x0 + 1 == H;
             const int o0 = y0 * S + x0, o1 = wrap ? (y0 + 1) * S : o0 + 1;
@@ -198,7 +206,7 @@ __device__ __forceinline__ void plane_copy(typename Cx<T>::t *Pl, typename Cx<T>
     if (!TO_LDS) {
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const int q = threadIdx.x + j * NTH;
+            const int q = tid + j * NTH;
             if (q < NPAIR) reinterpret_cast<Pair *>(g)[q] = v[j];
         }
     }
@@ -297,7 +305,8 @@ struct LseAcc {
 // thread 0 merges the wavefronts' results in order and stores the plane
 // partial.  red holds one entry per wavefront of the NTH-thread workgroup.
 template <typename T, int NTH = NT>
-__device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red, PlanePartial<T> *out) {
+__device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red, PlanePartial<T> *out,
+                                                    int tid = threadIdx.x) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         LseAcc<T> o;
@@ -308,9 +317,9 @@ __device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red,
         o.amin = __shfl_xor(a.amin, off);
         a.merge(o);
     }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    if ((tid & 63) == 0) red[tid >> 6] = a;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         LseAcc<T> r = red[0];
         for (int w = 1; w < NTH / 64; ++w) r.merge(red[w]);
         PlanePartial<T> o;

@@ -470,6 +470,32 @@ __global__ __launch_bounds__(NT) void k_lig_fwd_xy(const int32_t *__restrict__ f
     }
 }
 
+// Energy planes of the configurations marked in need[] (nneed[0] of them, a
+// count the host does not know): a grid of fixed size strides over the
+// forward items of the chunk (one per energy plane).
+template <typename T, int N>
+__global__ __launch_bounds__(NT) void k_lig_fwd_need(const int32_t *__restrict__ fwd_off, int n_cfg, int n_items,
+                                                      const CfgDev *__restrict__ cfgs,
+                                                      const int32_t *__restrict__ ulat, const T *__restrict__ gam,
+                                                      const typename Cx<T>::t *__restrict__ twg,
+                                                      typename Cx<T>::t *__restrict__ ws,
+                                                      const uint8_t *__restrict__ need,
+                                                      const int32_t *__restrict__ nneed) {
+    using C2 = typename Cx<T>::t;
+    constexpr int DEA = de_atoms<N>();
+    __shared__ C2 tab[DEA * (N / 2 + 1 + N)];
+    __shared__ C2 tw[N];
+    if (nneed[0] == 0) return;
+    load_tw<T, N>(tw, twg);
+    for (int item = (int)blockIdx.x; item < n_items; item += (int)gridDim.x) {
+        const int ic = find_cfg(fwd_off, n_cfg, item);
+        if (!need[ic]) continue;
+        const CfgDev c = cfgs[ic];
+        __syncthreads();
+        energy_plane_direct<T, N, DEA>(c, item - fwd_off[ic], ulat, gam, tw, tab, ws);
+    }
+}
+
 // Receptor xy pass: block b -> (channel, z) over n_ch * n_rec planes.
 template <typename T, int N>
 __global__ __launch_bounds__(NT) void k_rec_xy(const T *__restrict__ grids, const uint8_t *__restrict__ occ,
@@ -1467,14 +1493,6 @@ __global__ __launch_bounds__(NT) void k_reduce(const fftdg_partial *__restrict__
     }
 }
 
-// A copy of v the compiler cannot see through: index arithmetic derived from
-// it is recomputed where it is used instead of being hoisted out of loops and
-// held in registers across the whole kernel.
-__device__ __forceinline__ int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // Whole-plane inverse xy for the split-plane grid: one workgroup of WT = 1024
 // threads (64 FFT units of R1 = 16 lanes) per (configuration, valid z), so
 // each plane is read from device memory once and nothing is written back.
@@ -1990,6 +2008,14 @@ struct Launch {
                                ulat, (const T *)gam, thr, (const C2 *)tw, (C2 *)ws);
         return hipGetLastError();
     }
+    static hipError_t fwd_need(hipStream_t st, const int32_t *fwd_off, int n_cfg, int n_items, const CfgDev *cfgs,
+                               const int32_t *ulat, const void *gam, const void *tw, void *ws, const uint8_t *need,
+                               const int32_t *nneed) {
+        if (n_items <= 0) return hipSuccess;
+        hipLaunchKernelGGL((k_lig_fwd_need<T, N>), dim3(n_items < 1024 ? n_items : 1024), dim3(NT), 0, st, fwd_off,
+                           n_cfg, n_items, cfgs, ulat, (const T *)gam, (const C2 *)tw, (C2 *)ws, need, nneed);
+        return hipGetLastError();
+    }
     static hipError_t zprod(hipStream_t st, bool occ, bool edirect, int zhalf, const CfgDev *cfgs, const int32_t *zcfg,
                             int nz, const void *ws, const void *rspec, const void *tw, void *wsi,
                             const int32_t *ulat, const void *gam, int n_snap, int64_t spec_stride,
@@ -2099,6 +2125,7 @@ static const KernelSet *make_split_set() {
         Geo<T, N>::NP,
         LaunchSplit<T, N>::rec_spectra,
         LaunchSplit<T, N>::fwd,
+        nullptr,
         Launch<T, N>::zprod,
         LaunchSplit<T, N>::inv,
         Launch<T, N>::merge,
@@ -2115,6 +2142,7 @@ static const KernelSet *make_set() {
         Geo<T, N>::NP,
         Launch<T, N>::rec_spectra,
         Launch<T, N>::fwd,
+        Launch<T, N>::fwd_need,
         Launch<T, N>::zprod,
         Launch<T, N>::inv,
         Launch<T, N>::merge,
