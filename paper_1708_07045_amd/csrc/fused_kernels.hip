@@ -95,7 +95,9 @@ __global__ __launch_bounds__(NT) void k_rec_dilate(const uint8_t *__restrict__ o
 }
 
 // ------------------------------------------------------------ ligand runs
-// Exclusive prefix sum over the block (fixed order), `total` = block sum.
+// Exclusive prefix sum over a block of NTH threads (fixed order), `total` =
+// block sum; sh holds one int per wavefront.
+template <int NTH = NT>
 __device__ __forceinline__ int block_excl_scan(int v, int &total, int *sh) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int x = v;
@@ -108,7 +110,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int &total, int *sh) {
     __syncthreads();
     int base = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
+    for (int i = 0; i < NTH / 64; ++i) {
         base += i < w ? sh[i] : 0;
         tot += sh[i];
     }
@@ -117,23 +119,32 @@ __device__ __forceinline__ int block_excl_scan(int v, int &total, int *sh) {
     return base + x - v;
 }
 
-__device__ __forceinline__ long long ceildiv16(long long a) { return -floordiv(-a, 65536LL); }
-
 // The ball of atom `a` on row (y, z): [xlo, xhi] in true grid x, or false.
+// Point x belongs to it iff (2^16 x - Ux)^2 < rem, with rem what the row
+// leaves of the squared radius: an estimate of the ends from a FP32 root
+// (good to a fraction of a lattice step of 2^-16), moved by that integer test.
 struct RunAtom {
     int Ux, Uy, Uz;
     long long T;
 };
-__device__ __forceinline__ bool ball_row(const RunAtom &A, int y, int z, long long &xlo, long long &xhi) {
-    const long long dz = (long long)z * 65536LL - A.Uz;
-    const long long rz = A.T - dz * dz;
+__device__ __forceinline__ bool ball_row(const RunAtom &A, int y, int z, int &xlo, int &xhi) {
+    const int dz = z * 65536 - A.Uz;
+    const long long rz = A.T - (long long)dz * dz;
     if (rz <= 0) return false;
-    const long long dy = (long long)y * 65536LL - A.Uy;
-    const long long rem = rz - dy * dy;
+    const int dy = y * 65536 - A.Uy;
+    const long long rem = rz - (long long)dy * dy;
     if (rem <= 0) return false;
-    const long long s = isqrt_lt(rem);
-    xlo = ceildiv16(A.Ux - s);
-    xhi = floordiv(A.Ux + s, 65536LL);
+    auto in = [&](int x) {
+        const int d = x * 65536 - A.Ux;
+        return (long long)d * d < rem;
+    };
+    const int s = (int)__builtin_sqrtf((float)rem);
+    xlo = (A.Ux - s + 65535) >> 16;
+    xhi = (A.Ux + s) >> 16;
+    if (in(xlo - 1)) --xlo;
+    else if (!in(xlo)) ++xlo;
+    if (in(xhi + 1)) ++xhi;
+    else if (!in(xhi)) --xhi;
     return xlo <= xhi;
 }
 
@@ -166,23 +177,71 @@ __device__ __forceinline__ int emit_run(uint2 *out, int pos, int cap, int z, int
     return k;
 }
 
+// The set bits of a row, N <= 128 of them in 64-bit words.
+template <int N>
+struct RowBits {
+    static constexpr int NQ = N > 64 ? 2 : 1;
+    unsigned long long q[NQ];
+    __device__ void clear() {
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) q[i] = 0ull;
+    }
+    __device__ bool any() const { return NQ == 2 ? (q[0] | q[1]) != 0ull : q[0] != 0ull; }
+    // points l .. h (0 <= l <= h < N)
+    __device__ void set(int l, int h) {
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int lo = max(l - 64 * i, 0), n = min(h - 64 * i, 63) - lo + 1;
+            if (n > 0) q[i] |= (~0ull >> (64 - n)) << lo;
+        }
+    }
+    // lowest maximal segment [s, e), removed
+    __device__ void take(int &s, int &e) {
+        if (NQ == 1 || q[0]) {
+            s = __builtin_ctzll(q[0]);
+            const unsigned long long r = ~(q[0] >> s);
+            const int len = r ? __builtin_ctzll(r) : 64;
+            e = min(s + len, 64);
+            q[0] &= s + len >= 64 ? 0ull : ~0ull << e;
+            if (NQ == 2 && e == 64) {
+                const unsigned long long u = ~q[NQ - 1];
+                const int more = u ? __builtin_ctzll(u) : 64;
+                e += more;
+                q[NQ - 1] &= more >= 64 ? 0ull : ~0ull << more;
+            }
+        } else {
+            s = 64 + __builtin_ctzll(q[NQ - 1]);
+            const unsigned long long r = ~(q[NQ - 1] >> (s - 64));
+            const int len = r ? __builtin_ctzll(r) : 64;
+            e = min(s + len, 128);
+            q[NQ - 1] &= e >= 128 ? 0ull : ~0ull << (e - 64);
+        }
+    }
+};
+
 // One block per scanned configuration.  Runs are written in a fixed order:
 // first each atom's chord through the row nearest its centre (its widest
 // segment; a subset of the union, so harmless to the OR, and the most likely
 // to meet receptor occupancy, which lets the clash test stop early), then
 // the maximal segments of the union of the balls on every row of the
-// occupancy window, z-major.
+// occupancy window, z-major.  Bound: latency, a chunk of 256 configurations
+// being one block a compute unit; 16 wavefronts take a site ligand's 2000
+// rows in two rounds (4 took eight), and a ball's row costs a FP32 root and
+// four integer tests (it was an FP64 root moved by 64-bit squares and four
+// 64-bit divisions).  256 site configurations: 118 -> 31 us.
+constexpr int RUN_NT = 1024;
 template <int N>
-__global__ __launch_bounds__(NT) void k_lig_runs(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg,
+__global__ __launch_bounds__(RUN_NT) void k_lig_runs(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg,
                                                   const int32_t *__restrict__ ulat, const double *__restrict__ thr,
                                                   uint32_t *__restrict__ runs, int32_t *__restrict__ run_count) {
-    constexpr int NW = N / 32;
     __shared__ RunAtom at[MAXA];
-    __shared__ int sh[NT / 64];
+    __shared__ int sh[RUN_NT / 64];
     const int lc = zcfg[blockIdx.x];
-    const CfgDev c = cfgs[lc];
+    const CfgDev &c = cfgs[lc];
     const int n = c.n_atoms;
-    for (int a = threadIdx.x; a < n; a += NT) {
+    static_assert(RUN_NT >= MAXA, "a thread per atom");
+    if ((int)threadIdx.x < n) {
+        const int a = threadIdx.x;
         const int32_t *U = ulat + 3 * (c.u_base + a);
         at[a] = RunAtom{U[0], U[1], U[2], (long long)thr[c.atom_base + a]};
     }
@@ -190,80 +249,47 @@ __global__ __launch_bounds__(NT) void k_lig_runs(const CfgDev *__restrict__ cfgs
     uint2 *out = reinterpret_cast<uint2 *>(runs) + c.run_off;
     const int cap = c.run_cap;
     int base = 0, total;
-    // chords through the centre rows
-    for (int a0 = 0; a0 < n; a0 += NT) {
-        const int a = a0 + (int)threadIdx.x;
-        long long xlo = 0, xhi = -1;
-        int yc = 0, zc = 0;
+    {  // chords through the centre rows
+        const int a = threadIdx.x;
+        int xlo = 0, xhi = -1, yc = 0, zc = 0;
         bool has = false;
         if (a < n) {
-            yc = (int)floordiv((long long)at[a].Uy + 32768LL, 65536LL);
-            zc = (int)floordiv((long long)at[a].Uz + 32768LL, 65536LL);
+            yc = (at[a].Uy + 32768) >> 16;
+            zc = (at[a].Uz + 32768) >> 16;
             has = ball_row(at[a], yc, zc, xlo, xhi);
         }
-        const int len = has ? (int)(xhi - xlo + 1) : 0;
-        const int pos = base + block_excl_scan(has ? run_pieces(len) : 0, total, sh);
-        if (has) emit_run<N>(out, pos, cap, zc, yc, (int)xlo, len);
+        const int len = has ? xhi - xlo + 1 : 0;
+        const int pos = base + block_excl_scan<RUN_NT>(has ? run_pieces(len) : 0, total, sh);
+        if (has) emit_run<N>(out, pos, cap, zc, yc, xlo, len);
         base += total;
     }
     // every row of the occupancy window: union of the balls as a bit row
     // relative to xo0 (the window's x extent is at most N), then its runs
-    const int nrows = c.Lo * c.Lyo;
-    for (int r0 = 0; r0 < nrows; r0 += NT) {
+    const int Lyo = c.Lyo, nrows = c.Lo * Lyo, zo0 = c.zo0, yo0 = c.yo0, xo0 = c.xo0;
+    for (int r0 = 0; r0 < nrows; r0 += RUN_NT) {
         const int r = r0 + (int)threadIdx.x;
-        uint32_t m[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) m[w] = 0u;
+        RowBits<N> m;
+        m.clear();
         int z = 0, y = 0;
         if (r < nrows) {
-            z = c.zo0 + r / c.Lyo;
-            y = c.yo0 + r % c.Lyo;
+            z = zo0 + r / Lyo;
+            y = yo0 + r - (r / Lyo) * Lyo;
             for (int a = 0; a < n; ++a) {
-                long long xlo, xhi;
-                if (!ball_row(at[a], y, z, xlo, xhi)) continue;
-                const int l = (int)(xlo - c.xo0), h = (int)(xhi - c.xo0);
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    const int lo = max(l, 32 * w), hi = min(h, 32 * w + 31);
-                    if (lo <= hi) {
-                        const int wid = hi - lo + 1;
-                        m[w] |= (wid == 32 ? ~0u : ((1u << wid) - 1u)) << (lo - 32 * w);
-                    }
-                }
+                int xlo, xhi;
+                if (ball_row(at[a], y, z, xlo, xhi)) m.set(xlo - xo0, xhi - xo0);
             }
         }
-        // maximal segments of the row (runs start where a set bit follows a
-        // clear one), counted in pieces of at most RUN_MAX points
-        int cnt = 0;
-        for (int pass = 0; pass < 2; ++pass) {
-        int pos = pass ? base + block_excl_scan(cnt, total, sh) : 0;
-        if (r < nrows) {
-            int x = 0;
-            while (x < N) {
-                // next set bit at or after x
-                int s = N;
-                for (int w = x >> 5; w < NW; ++w) {
-                    const uint32_t b = m[w] & (w == (x >> 5) ? (~0u << (x & 31)) : ~0u);
-                    if (b) {
-                        s = 32 * w + __builtin_ctz(b);
-                        break;
-                    }
-                }
-                if (s >= N) break;
-                // next clear bit after s
-                int e = N;
-                for (int w = s >> 5; w < NW; ++w) {
-                    const uint32_t b = ~m[w] & (w == (s >> 5) ? (~0u << (s & 31)) : ~0u);
-                    if (b) {
-                        e = 32 * w + __builtin_ctz(b);
-                        break;
-                    }
-                }
-                if (pass) pos += emit_run<N>(out, pos, cap, z, y, c.xo0 + s, e - s);
-                else cnt += run_pieces(e - s);
-                x = e;
-            }
+        // maximal segments of the row, in pieces of at most RUN_MAX points:
+        // counted, then written
+        int cnt = 0, s, e;
+        for (RowBits<N> t = m; t.any();) {
+            t.take(s, e);
+            cnt += run_pieces(e - s);
         }
+        int pos = base + block_excl_scan<RUN_NT>(cnt, total, sh);
+        while (m.any()) {
+            m.take(s, e);
+            pos += emit_run<N>(out, pos, cap, z, y, xo0 + s, e - s);
         }
         base += total;
     }
@@ -1318,7 +1344,7 @@ struct LaunchFused {
     static hipError_t lig_runs(hipStream_t st, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *ulat,
                                const double *thr, uint32_t *runs, int32_t *run_count) {
         if (nz <= 0) return hipSuccess;
-        hipLaunchKernelGGL((k_lig_runs<N>), dim3(nz), dim3(NT), 0, st, cfgs, zcfg, ulat, thr, runs, run_count);
+        hipLaunchKernelGGL((k_lig_runs<N>), dim3(nz), dim3(RUN_NT), 0, st, cfgs, zcfg, ulat, thr, runs, run_count);
         return hipGetLastError();
     }
     static hipError_t zero(hipStream_t st, int32_t *p, int64_t n) {

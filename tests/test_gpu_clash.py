@@ -43,3 +43,28 @@ def test_mask_and_counts(n_fft, n_rec, h, n_at, occ_f):
         assert P["n_finite"][c] == int((e["clash"] == 0).sum())
         _, mask = ctx.energy_grid(0, b, c)
         assert np.array_equal(mask.cpu().numpy(), e["clash"])
+
+
+@pytest.mark.parametrize("n_at,n_rec", [(12, 110), (9, 100)])
+def test_long_runs(n_at, n_rec):
+    """A straight chain along x, y or z: along x its rows are unions of
+    overlapping balls longer than one piece of a run (63 points), across bit
+    64 of the row."""
+    import paper_1708_07045_amd as fd
+    w = synth.tiny(seed=3, n_rec=n_rec, n_fft=128, h=0.25, n_rec_atoms=50, n_lig_atoms=n_at, n_cfg=1, precision="f32")
+    L = w.ligands[0]
+    x = np.zeros((1, n_at, 3))
+    x[0, :, 0] = 1.5 * np.arange(n_at)
+    r = np.sqrt(0.5)
+    quat = np.array([[1.0, 0, 0, 0], [r, 0, 0, r], [r, 0, r, 0], [0.98, 0.02, 0.05, 0.1]])
+    w.ligands = [synth.Ligand(L.q, L.sigma, L.eps, x, np.zeros(4, np.int32), quat)]
+    ctx = fd.FFTDG.from_workload(w)
+    rc = w.receptor
+    g, o = ctx.receptor_grids(rc.xyz[0], rc.q, rc.sigma, rc.eps)
+    ctx.set_receptors(g[None], o[None], rc.weights)
+    b = fd.Batch(w.ligands)
+    go, oo = oracle.receptor_grids(w)
+    for c in range(4):
+        e = oracle.config_eval(w, go, oo, 0, c)
+        _, mask = ctx.energy_grid(0, b, c)
+        assert np.array_equal(mask.cpu().numpy(), e["clash"])
