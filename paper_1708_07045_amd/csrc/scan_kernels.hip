@@ -24,6 +24,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/fftdg.h"
 #include "fft_device.hpp"
 #include "kernels.hpp"
@@ -1931,6 +1933,10 @@ __global__ __launch_bounds__(NT) void k_pair_energies(int n_rec_atoms, const dou
 // two radii as thresholds on the squared distance.  1/r comes from the
 // hardware estimate and one third-order step, its powers by multiplication,
 // and pairs past both radii (all but a few in a hundred) need no select.
+// FP64 grids (T double) are the plain quotients added in the atoms' order,
+// one point and one wavefront: where charges cancel, a grid point is a
+// millionth of its terms, and any other rounding or order shows there in the
+// tenth digit.  FP32 grids round the sum, which hides it.
 // Bound: FP64 issue, 18 instructions a pair (three divisions, a root and the
 // atom's own roots and powers in every pair made it about 130).  2600 atoms
 // on 96^3 points: 7.3 -> 2.0 ms, on 248^3: 115 -> 31.8 ms (2.9 -> 0.80 ps a
@@ -1965,6 +1971,8 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
     struct alignas(16) Atom {
         double x, y, z, ele, ljr, lja, rex2, occ2, near2, pad;
     };
+    constexpr bool PLAIN = std::is_same<T, double>::value;
+    static_assert(!PLAIN || RG_S == 1, "FP64 grids are summed in the atoms' order");
     constexpr int NS = RG_NT * RG_S;  // threads, and atoms staged at once
     __shared__ Atom at[NS];
     const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / RG_NT), pt = (int)threadIdx.x % RG_NT;
@@ -2011,6 +2019,24 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
                 d2[k] = dx * dx + dy2 + dz2;
                 near = near || !(d2[k] >= A.near2);
             }
+            auto quotients = [&](const Atom &A, int k) {
+                const double r = sqrt(d2[k]), r6 = r * r * r * r * r * r;
+                if (d2[k] >= A.rex2) {
+                    ele[k] += A.ele / r;
+                    lja[k] += A.lja / r6;
+                    ljr[k] += A.ljr / (r6 * r6);
+                } else if (CAP) {
+                    ljr[k] += A.ljr / (r6 * r6);
+                }
+            };
+            if constexpr (PLAIN) {
+#pragma unroll
+                for (int k = 0; k < RG_P; ++k) {
+                    if (d2[k] < A.occ2) hit[k] = 1;
+                    quotients(A, k);
+                }
+                continue;
+            }
             if (__any(near)) {  // wave-uniform: a few atoms in a hundred
                 bool odd = !(A.near2 < INFINITY);
 #pragma unroll
@@ -2035,16 +2061,7 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
                 // a point on the atom (or nowhere), or a numerator that is not
                 // finite and must not meet a zero: the plain quotients
 #pragma unroll 1
-                for (int k = 0; k < RG_P; ++k) {
-                    const double r = sqrt(d2[k]), r6 = r * r * r * r * r * r;
-                    if (d2[k] >= A.rex2) {
-                        ele[k] += A.ele / r;
-                        lja[k] += A.lja / r6;
-                        ljr[k] += A.ljr / (r6 * r6);
-                    } else if (CAP) {
-                        ljr[k] += A.ljr / (r6 * r6);
-                    }
-                }
+                for (int k = 0; k < RG_P; ++k) quotients(A, k);
                 continue;
             }
 #pragma unroll
@@ -2350,8 +2367,8 @@ hipError_t launch_receptor_grids(hipStream_t st, int precision, int n_atoms, con
         if (mode == 1) { FFTDG_RG(float, true) }
         else { FFTDG_RG(float, false) }
     } else {
-        if (mode == 1) { FFTDG_RG(double, true) }
-        else { FFTDG_RG(double, false) }
+        if (mode == 1) FFTDG_RGP(double, true, 1, 1)
+        else FFTDG_RGP(double, false, 1, 1)
     }
 #undef FFTDG_RG
 #undef FFTDG_RGP
