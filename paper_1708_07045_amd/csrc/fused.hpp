@@ -48,6 +48,19 @@ struct Dil {
 // LDS budget of the per-block factor table of the fused z kernel.
 constexpr size_t FUSED_TABLE_BYTES = 16384;
 
+// Strides between the snapshots of one launch (blockIdx.y) of the clash
+// test and the direct energies.
+struct SnapStride {
+    int64_t dil;    // words of a receptor bit table
+    int64_t fb;     // words of free bits
+    int64_t live;   // bytes of live flags
+    int64_t surv;   // slots of the undecided-row lists
+    int64_t counts; // ints of the counts (scnt, fcnt, out)
+    int64_t zlist;  // ints of the list of configurations that take the transforms
+    int64_t grid;   // elements of the receptor grids
+    int64_t pp;     // plane partials
+};
+
 struct FusedSet {
     int n_fft;
     int64_t dil_words;  // words of one snapshot's dilation table
@@ -64,25 +77,26 @@ struct FusedSet {
     // phase-1 items (tz, 64-row group), item2_off those of the phase-2 items
     // (64-row slices of a configuration's undecided-row list); surv holds the
     // lists (at surv_off), scnt their lengths, fcnt the free translations per
-    // configuration (n_cfg ints each, zero on entry)
-    hipError_t (*clash)(hipStream_t, const int32_t *item_off, const int32_t *item2_off, int n_cfg, int n_items,
-                        int n_items2, const CfgDev *cfgs, const uint32_t *runs, const int32_t *run_count,
-                        const uint32_t *dil, uint32_t *fb, uint8_t *live, uint32_t *surv, int32_t *scnt,
-                        int32_t *fcnt);
+    // configuration (n_cfg ints each, zero on entry); ns snapshots a launch
+    hipError_t (*clash)(hipStream_t, int ns, const SnapStride &st, const int32_t *item_off, const int32_t *item2_off,
+                        int n_cfg, int n_items, int n_items2, const CfgDev *cfgs, const uint32_t *runs,
+                        const int32_t *run_count, const uint32_t *dil, uint32_t *fb, uint8_t *live, uint32_t *surv,
+                        int32_t *scnt, int32_t *fcnt);
     // direct energies: per scanned configuration its atoms' corner offsets
     // and weights (nz x max_atoms records of corner_bytes); which
     // configurations go through the transforms (zlist, need, out[2] as
     // k_modes writes them; done: one int per configuration, zero at the
     // chunk's start); Eq. 2 plane partials of the others from the receptor
-    // grids [3][n_rec^3]
+    // grids [3][n_rec^3].  ns snapshots a launch; need and out[1] are for all
+    // of them together
     size_t corner_bytes;
     hipError_t (*corner_atoms)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
                                const int32_t *ulat, const void *gam, int n_rec, void *atoms);
-    hipError_t (*modes)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *fcnt,
-                        int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out);
-    hipError_t (*direct)(hipStream_t, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
-                         const void *atoms, int max_atoms, const void *grids, int n_rec, double beta,
-                         const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp);
+    hipError_t (*modes)(hipStream_t, int ns, const SnapStride &st, const CfgDev *cfgs, const int32_t *zcfg, int nz,
+                        const int32_t *fcnt, int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out);
+    hipError_t (*direct)(hipStream_t, int ns, const SnapStride &st, const int32_t *inv_off, int n_cfg, int n_items,
+                         const CfgDev *cfgs, const void *atoms, int max_atoms, const void *grids, int n_rec,
+                         double beta, const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp);
     // per scanned configuration of a chunk: its atoms sorted by plane with
     // their x/y placement and channel weights, and the plane starts
     // (zat: nz x max_atoms records, zbt: nz x (N + 2) ints)

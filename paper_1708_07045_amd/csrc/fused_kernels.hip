@@ -443,9 +443,11 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
                                                 const int32_t *__restrict__ run_count,
                                                 const uint32_t *__restrict__ dil, uint32_t *__restrict__ fb,
                                                 uint8_t *__restrict__ live, uint32_t *__restrict__ surv,
-                                                int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt) {
+                                                int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt, SnapStride st) {
     using D = Dil<N>;
     constexpr int NW = D::NW;
+    dil += blockIdx.y * st.dil, fb += blockIdx.y * st.fb, live += blockIdx.y * st.live;
+    surv += blockIdx.y * st.surv, scnt += blockIdx.y * st.counts, fcnt += blockIdx.y * st.counts;
     const int item = (int)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (item >= n_items) return;
     const int lane = threadIdx.x & 63;
@@ -520,8 +522,11 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
                                                 const int32_t *__restrict__ run_count,
                                                 const uint32_t *__restrict__ dil, uint32_t *__restrict__ fb,
                                                 uint8_t *__restrict__ live, const uint32_t *__restrict__ surv,
-                                                const int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt) {
+                                                const int32_t *__restrict__ scnt, int32_t *__restrict__ fcnt,
+                                                SnapStride st) {
     using D = Dil<N>;
+    dil += blockIdx.y * st.dil, fb += blockIdx.y * st.fb, live += blockIdx.y * st.live;
+    surv += blockIdx.y * st.surv, scnt += blockIdx.y * st.counts, fcnt += blockIdx.y * st.counts;
     constexpr int NW = D::NW, NWV = NT / 64;
     __shared__ uint32_t sacc[NW][64];
     const int item = (int)blockIdx.x;
@@ -645,37 +650,38 @@ __global__ __launch_bounds__(NT) void k_corner_atoms(const CfgDev *__restrict__ 
     out[(int64_t)zi * ma + a] = r;
 }
 
-// The configurations of one (chunk, snapshot) that go through the transforms:
-// zlist[0 .. out[0]) their indices among the scanned ones, in order;
-// need[local] = 1 for those whose forward planes are not there yet (out[1]
-// of them), noted in done.  One block.
+// The configurations of a chunk that go through the transforms, per snapshot
+// (the launch's ns of them, strides st): zlist[0 .. out[0]) their indices
+// among the scanned ones, in order; need[local] = 1 for those whose forward
+// planes are not there yet (out[1] of the first snapshot of them), noted in
+// done.  One block.
 template <typename T, int N>
 __global__ __launch_bounds__(NT) void k_modes(const CfgDev *__restrict__ cfgs, const int32_t *__restrict__ zcfg, int nz,
                                               const int32_t *__restrict__ fcnt, int32_t *__restrict__ done,
                                               int32_t *__restrict__ zlist, uint8_t *__restrict__ need,
-                                              int32_t *__restrict__ out) {
+                                              int32_t *__restrict__ out, int ns, SnapStride st) {
     __shared__ int sh[NT / 64];
-    int base = 0, nneed = 0, total;
-    for (int z0 = 0; z0 < nz; z0 += NT) {
-        const int zi = z0 + (int)threadIdx.x;
-        int l = 0;
-        bool fft = false, nd = false;
-        if (zi < nz) {
-            l = zcfg[zi];
-            fft = by_transforms<T, N>(fcnt[l], cfgs[l].n_atoms);
-            nd = fft && done[l] == 0;
-            need[l] = nd ? 1 : 0;
-            if (nd) done[l] = 1;
+    int nneed = 0, total;
+    for (int s = 0; s < ns; ++s) {
+        int base = 0;
+        for (int z0 = 0; z0 < nz; z0 += NT) {
+            const int zi = z0 + (int)threadIdx.x;
+            bool fft = false, nd = false;
+            if (zi < nz) {
+                const int l = zcfg[zi];
+                fft = by_transforms<T, N>(fcnt[s * st.counts + l], cfgs[l].n_atoms);
+                nd = fft && done[l] == 0;  // each configuration by one thread throughout
+                if (nd) done[l] = 1;
+                if (s == 0 || nd) need[l] = nd ? 1 : 0;
+            }
+            const int pos = base + block_excl_scan(fft ? 1 : 0, total, sh);
+            if (fft) zlist[s * st.zlist + pos] = zi;
+            base += total;
+            nneed += __syncthreads_count(nd);
         }
-        const int pos = base + block_excl_scan(fft ? 1 : 0, total, sh);
-        if (fft) zlist[pos] = zi;
-        base += total;
-        nneed += __syncthreads_count(nd);
+        if (threadIdx.x == 0) out[s * st.counts] = base;
     }
-    if (threadIdx.x == 0) {
-        out[0] = base;
-        out[1] = nneed;
-    }
+    if (threadIdx.x == 0) out[1] = nneed;
 }
 
 // One block per (configuration, box-valid z-translation): the plane's free
@@ -693,7 +699,9 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
     const int32_t *__restrict__ inv_off, int n_cfg, const CfgDev *__restrict__ cfgs,
     const CornerAtom<T> *__restrict__ atoms, int ma, const T *__restrict__ grids, int n_rec, T beta,
     const uint32_t *__restrict__ fb, const uint8_t *__restrict__ live, const int32_t *__restrict__ fcnt,
-    PlanePartial<T> *__restrict__ pp) {
+    PlanePartial<T> *__restrict__ pp, SnapStride st) {
+    grids += blockIdx.y * st.grid, fb += blockIdx.y * st.fb, live += blockIdx.y * st.live;
+    fcnt += blockIdx.y * st.counts, pp += blockIdx.y * st.pp;
     constexpr int ND = direct_threads<N>(), NW = N / 32;
     constexpr int MAXW = N * NW;                   // words of a plane's free bits
     constexpr int PER = (MAXW + ND - 1) / ND;
@@ -1352,16 +1360,16 @@ struct LaunchFused {
         hipLaunchKernelGGL(k_zero32, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, st, p, (int)n);
         return hipGetLastError();
     }
-    static hipError_t clash(hipStream_t st, const int32_t *item_off, const int32_t *item2_off, int n_cfg,
-                            int n_items, int n_items2, const CfgDev *cfgs, const uint32_t *runs,
-                            const int32_t *run_count, const uint32_t *dil, uint32_t *fb, uint8_t *live,
-                            uint32_t *surv, int32_t *scnt, int32_t *fcnt) {
+    static hipError_t clash(hipStream_t st, int ns, const SnapStride &ss, const int32_t *item_off,
+                            const int32_t *item2_off, int n_cfg, int n_items, int n_items2, const CfgDev *cfgs,
+                            const uint32_t *runs, const int32_t *run_count, const uint32_t *dil, uint32_t *fb,
+                            uint8_t *live, uint32_t *surv, int32_t *scnt, int32_t *fcnt) {
         if (n_items <= 0) return hipSuccess;
-        hipLaunchKernelGGL((k_clash1<N>), dim3((n_items + NT / 64 - 1) / (NT / 64)), dim3(NT), 0, st, item_off,
-                           n_cfg, n_items, cfgs, runs, run_count, dil, fb, live, surv, scnt, fcnt);
+        hipLaunchKernelGGL((k_clash1<N>), dim3((n_items + NT / 64 - 1) / (NT / 64), ns), dim3(NT), 0, st, item_off,
+                           n_cfg, n_items, cfgs, runs, run_count, dil, fb, live, surv, scnt, fcnt, ss);
         if (n_items2 > 0)
-            hipLaunchKernelGGL((k_clash2<N>), dim3(n_items2), dim3(NT), 0, st, item2_off, n_cfg, n_items2, cfgs, runs,
-                               run_count, dil, fb, live, surv, scnt, fcnt);
+            hipLaunchKernelGGL((k_clash2<N>), dim3(n_items2, ns), dim3(NT), 0, st, item2_off, n_cfg, n_items2, cfgs,
+                               runs, run_count, dil, fb, live, surv, scnt, fcnt, ss);
         return hipGetLastError();
     }
     static hipError_t corner_atoms(hipStream_t st, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
@@ -1371,18 +1379,19 @@ struct LaunchFused {
                            st, cfgs, zcfg, nz, max_atoms, ulat, (const T *)gam, n_rec, (CornerAtom<T> *)atoms);
         return hipGetLastError();
     }
-    static hipError_t modes(hipStream_t st, const CfgDev *cfgs, const int32_t *zcfg, int nz, const int32_t *fcnt,
-                            int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out) {
-        hipLaunchKernelGGL((k_modes<T, N>), dim3(1), dim3(NT), 0, st, cfgs, zcfg, nz, fcnt, done, zlist, need, out);
+    static hipError_t modes(hipStream_t st, int ns, const SnapStride &ss, const CfgDev *cfgs, const int32_t *zcfg,
+                            int nz, const int32_t *fcnt, int32_t *done, int32_t *zlist, uint8_t *need, int32_t *out) {
+        hipLaunchKernelGGL((k_modes<T, N>), dim3(1), dim3(NT), 0, st, cfgs, zcfg, nz, fcnt, done, zlist, need, out,
+                           ns, ss);
         return hipGetLastError();
     }
-    static hipError_t direct(hipStream_t st, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
-                             const void *atoms, int max_atoms, const void *grids, int n_rec, double beta,
+    static hipError_t direct(hipStream_t st, int ns, const SnapStride &ss, const int32_t *inv_off, int n_cfg,
+                             int n_items, const CfgDev *cfgs, const void *atoms, int max_atoms, const void *grids, int n_rec, double beta,
                              const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp) {
         if (n_items <= 0) return hipSuccess;
-        hipLaunchKernelGGL((k_direct<T, N>), dim3(n_items), dim3(direct_threads<N>()), 0, st, inv_off, n_cfg, cfgs,
+        hipLaunchKernelGGL((k_direct<T, N>), dim3(n_items, ns), dim3(direct_threads<N>()), 0, st, inv_off, n_cfg, cfgs,
                            (const CornerAtom<T> *)atoms, max_atoms, (const T *)grids, n_rec, (T)beta, fb, live, fcnt,
-                           (PlanePartial<T> *)pp);
+                           (PlanePartial<T> *)pp, ss);
         return hipGetLastError();
     }
     static int atoms_per_table() {

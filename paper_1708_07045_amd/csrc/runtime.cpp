@@ -768,15 +768,23 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     const int nsets = overlap ? 2 : 1;
     const size_t e_free = (size_t)std::max<int64_t>(P.max_free, 1), e_items = (size_t)std::max<int64_t>(P.max_items, 1);
     const size_t e_surv = (size_t)std::max<int64_t>(P.max_surv, 1), e_cfgs = (size_t)std::max<int64_t>(P.max_chunk_cfgs, 1);
+    const int s_begin = snap_only >= 0 ? snap_only : 0;
+    const int s_end = snap_only >= 0 ? snap_only + 1 : ctx->n_snap;
+    // snapshots of one launch of the clash test and the direct energies: as
+    // many as keep a buffer set under half a GiB and the workspace limit.  One
+    // snapshot of a chunk does not fill the chip on a coarse grid, and each
+    // launch costs its gap: 24 chunks of 5 snapshots at 64^3 12.0 -> 8.3 ms,
+    // 10 snapshots of 24 ligands at 128^3 29 -> 27 ms
+    const size_t set_bytes = sizeof(uint32_t) * (e_free + e_surv) + e_items;
+    const size_t set_room = std::min<size_t>(std::min(ctx->ws_limit, (size_t)512 << 20) / set_bytes, 65535);  // grid.y
+    const int sgrp = P.fused && occ ? (int)std::max<size_t>(1, std::min<size_t>((size_t)(s_end - s_begin), set_room)) : 1;
     if (P.fused && occ) {
         if ((rc = reserve(ctx, ctx->runs, 2 * sizeof(uint32_t) * (size_t)std::max<int64_t>(P.max_runs, 1)))) return rc;
         if ((rc = reserve(ctx, ctx->run_cnt, sizeof(int32_t) * e_cfgs))) return rc;
-        if ((rc = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets))) return rc;
-        if ((rc = reserve(ctx, ctx->lives, e_items * nsets))) return rc;
-        if ((rc = reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets))) return rc;
+        if ((rc = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets * sgrp))) return rc;
+        if ((rc = reserve(ctx, ctx->lives, e_items * nsets * sgrp))) return rc;
+        if ((rc = reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets * sgrp))) return rc;
     }
-    const int s_begin = snap_only >= 0 ? snap_only : 0;
-    const int s_end = snap_only >= 0 ? snap_only + 1 : ctx->n_snap;
     // hybrid: energies summed directly at the clash-free translations where
     // they are few, through the transforms otherwise, decided on the device
     // per configuration and snapshot.  Its counts start at zero, one clear for
@@ -798,7 +806,7 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     }
     if (hybrid) {
         if ((rc = reserve(ctx, ctx->corners, ctx->fs->corner_bytes * (size_t)max_nz_atoms))) return rc;
-        if ((rc = reserve(ctx, ctx->zlist, sizeof(int32_t) * (size_t)nzmax * nsets))) return rc;
+        if ((rc = reserve(ctx, ctx->zlist, sizeof(int32_t) * (size_t)nzmax * nsets * sgrp))) return rc;
         if ((rc = reserve(ctx, ctx->need, e_cfgs * nsets))) return rc;
     }
     if (overlap && !ctx->side) {
@@ -856,11 +864,11 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     uint32_t *runs = (uint32_t *)ctx->runs.p;
     int32_t *rcnt = (int32_t *)ctx->run_cnt.p;
     const double b_spec3 = 3.0 * (double)g.n_fft * ctx->ks->np * cb;
-    // buffer set p of the clash results
-    auto fb_of = [&](int p) { return (uint32_t *)ctx->fbits.p + (size_t)p * e_free; };
-    auto lv_of = [&](int p) { return (uint8_t *)ctx->lives.p + (size_t)p * e_items; };
-    auto surv_of = [&](int p) { return (uint32_t *)ctx->surv.p + (size_t)p * e_surv; };
-    auto zlist_of = [&](int p) { return (int32_t *)ctx->zlist.p + (size_t)p * nzmax; };
+    // buffer set p of the clash results, snapshot k of its group
+    auto fb_of = [&](int p, int k) { return (uint32_t *)ctx->fbits.p + (size_t)(p * sgrp + k) * e_free; };
+    auto lv_of = [&](int p, int k) { return (uint8_t *)ctx->lives.p + (size_t)(p * sgrp + k) * e_items; };
+    auto surv_of = [&](int p) { return (uint32_t *)ctx->surv.p + (size_t)(p * sgrp) * e_surv; };
+    auto zlist_of = [&](int p, int k) { return (int32_t *)ctx->zlist.p + (size_t)(p * sgrp + k) * nzmax; };
     auto need_of = [&](int p) { return (uint8_t *)ctx->need.p + (size_t)p * e_cfgs; };
     const size_t n3 = (size_t)g.n_rec * g.n_rec * g.n_rec;
     // stream of the occupancy runs and the clash test; with the overlap it
@@ -877,6 +885,8 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         const CfgDev *ccfg = dcfg + ch.c0;
         const int nloc = ch.c1 - ch.c0;
         int32_t *done = occ ? (int32_t *)ctx->counts.p + count_off[&ch - P.chunks.data()] : nullptr;
+        const SnapStride ss{(int64_t)fs->dil_words, (int64_t)e_free, (int64_t)e_items, (int64_t)e_surv, 2 * nloc + 2,
+                            nzmax, (int64_t)(3 * n3), (int64_t)(pp_snap / ctx->ks->ppbytes)};
         // the runs of this chunk follow the previous chunk's clash tests on `sc`
         if (occ)
             HIPCHK(ctx, timed(ctx, FFTDG_K_RUNS, 8.0 * (double)ch.nruns, [&] {
@@ -897,37 +907,36 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
                        return fs->zprep(st, ccfg, dz + ch.z0, (int)ch.nz, std::max(ch.max_atoms, 1), du, dgam,
                                         ctx->zat.p, (int32_t *)ctx->zbt.p);
                    }));
-        for (int s = s_begin; s < s_end; ++s, ++item) {
+        for (int s0 = s_begin; s0 < s_end; s0 += sgrp, ++item) {
+            const int ns = std::min(sgrp, s_end - s0);
             const int p = overlap ? (item & 1) : 0;
-            uint32_t *fb = fb_of(p);
-            uint8_t *lv = lv_of(p);
-            int32_t *scnt = occ ? done + nloc + (size_t)(s - s_begin) * (2 * nloc + 2) : nullptr;
+            int32_t *scnt = occ ? done + nloc + (size_t)(s0 - s_begin) * (2 * nloc + 2) : nullptr;
             int32_t *fcnt = occ ? scnt + nloc : nullptr, *mode = occ ? fcnt + nloc : nullptr;
             if (occ) {
-                // set p was last read by the inverse of item - 2
+                // set p was last read by the direct energies and transforms of item - 2
                 if (overlap && item >= 2) HIPCHK(ctx, hipStreamWaitEvent(sc, ctx->ev_main[p], 0));
-                const uint32_t *dil = (const uint32_t *)ctx->dil.p + (size_t)s * (size_t)fs->dil_words;
-                HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, 4.0 * (double)ch.nfree + (double)ch.nitems, [&] {
-                           return fs->clash(sc, ditem + ch.off0, ditem2 + ch.off0, nloc, ch.nitems, ch.nitems2, ccfg,
-                                            runs, rcnt, dil, fb, lv, surv_of(p), scnt, fcnt);
+                const uint32_t *dil = (const uint32_t *)ctx->dil.p + (size_t)s0 * (size_t)fs->dil_words;
+                HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, ns * (4.0 * (double)ch.nfree + (double)ch.nitems), [&] {
+                           return fs->clash(sc, ns, ss, ditem + ch.off0, ditem2 + ch.off0, nloc, ch.nitems, ch.nitems2,
+                                            ccfg, runs, rcnt, dil, fb_of(p, 0), lv_of(p, 0), surv_of(p), scnt, fcnt);
                        }));
                 if (hybrid)
-                    HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, 4.0 * (double)ch.nz, [&] {
-                               return fs->modes(sc, ccfg, dz + ch.z0, (int)ch.nz, fcnt, done, zlist_of(p), need_of(p),
-                                                mode);
+                    HIPCHK(ctx, timed(ctx, FFTDG_K_CLASH, ns * 4.0 * (double)ch.nz, [&] {
+                               return fs->modes(sc, ns, ss, ccfg, dz + ch.z0, (int)ch.nz, fcnt, done, zlist_of(p, 0),
+                                                need_of(p), mode);
                            }));
                 if (overlap) {
                     HIPCHK(ctx, hipEventRecord(ctx->ev_side[p], sc));
                     HIPCHK(ctx, hipStreamWaitEvent(st, ctx->ev_side[p], 0));
                 }
             }
-            const char *rs = (const char *)ctx->rspec.p + spec_per_snap * s;
-            void *pp_s = (char *)ctx->pp.p + pp_snap * (size_t)(s - s_begin);
+            auto pp_of = [&](int s) { return (void *)((char *)ctx->pp.p + pp_snap * (size_t)(s - s_begin)); };
             if (hybrid) {
-                HIPCHK(ctx, timed(ctx, FFTDG_K_INV, 3.0 * (double)(n3 * tsz) + 4.0 * (double)ch.nfree + pb * ch.pp, [&] {
-                           return fs->direct(st, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->corners.p,
-                                             std::max(ch.max_atoms, 1), (const char *)ctx->rgrid.p + 3 * n3 * tsz * s,
-                                             g.n_rec, beta, fb, lv, fcnt, pp_s);
+                const double b_dir = ns * (3.0 * (double)(n3 * tsz) + 4.0 * (double)ch.nfree + pb * ch.pp);
+                HIPCHK(ctx, timed(ctx, FFTDG_K_INV, b_dir, [&] {
+                           return fs->direct(st, ns, ss, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->corners.p,
+                                             std::max(ch.max_atoms, 1), (const char *)ctx->rgrid.p + 3 * n3 * tsz * s0,
+                                             g.n_rec, beta, fb_of(p, 0), lv_of(p, 0), fcnt, pp_of(s0));
                        }));
                 if (P.fused_planes)
                     HIPCHK(ctx, timed(ctx, FFTDG_K_FWD, 0.0, [&] {
@@ -935,26 +944,30 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
                                                    ctx->ws_fwd.p, need_of(p), mode + 1);
                            }));
             }
-            // planes written are counted on the device (those the inverse reads);
-            // in a hybrid scan these are all of the z pass's and the inverse's bytes
-            const double b_z = hybrid ? 0.0 : b_spec3 + (P.fused_planes ? (double)ch.ws_fwd * cb : 0.0);
-            HIPCHK(ctx, timed(ctx, FFTDG_K_ZPROD, b_z, [&] {
-                       if (P.fused_planes)
-                           return fs->zplanes(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
-                                              ctx->ws_fwd.p, rs, ctx->tw.p, ctx->ws_inv.p, lv,
-                                              hybrid ? zlist_of(p) : nullptr, mode);
-                       return fs->zpass(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
-                                        std::max(ch.max_atoms, 1), ctx->zat.p, (const int32_t *)ctx->zbt.p, rs,
-                                        ctx->tw.p, ctx->ws_inv.p, lv, hybrid ? zlist_of(p) : nullptr, mode);
-                   }));
-            HIPCHK(ctx, timed(ctx, FFTDG_K_INV, hybrid ? 0.0 : pb * ch.pp, [&] {
-                       return fs->inv(st, occ, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->ws_inv.p, beta,
-                                      ctx->tw.p, fb, lv, pp_s, psi_out, clash_out,
-                                      ctx->prof ? (unsigned int *)ctx->prof_cnt.p : nullptr, hybrid ? fcnt : nullptr,
-                                      mode);
-                   }));
+            for (int s = s0; s < s0 + ns; ++s) {
+                const int k = s - s0;
+                const int32_t *zl = hybrid ? zlist_of(p, k) : nullptr, *fc = hybrid ? fcnt + k * ss.counts : nullptr,
+                              *md = hybrid ? mode + k * ss.counts : nullptr;
+                const char *rs = (const char *)ctx->rspec.p + spec_per_snap * s;
+                // planes written are counted on the device (those the inverse reads);
+                // in a hybrid scan these are all of the z pass's and the inverse's bytes
+                const double b_z = hybrid ? 0.0 : b_spec3 + (P.fused_planes ? (double)ch.ws_fwd * cb : 0.0);
+                HIPCHK(ctx, timed(ctx, FFTDG_K_ZPROD, b_z, [&] {
+                           if (P.fused_planes)
+                               return fs->zplanes(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                                                  ctx->ws_fwd.p, rs, ctx->tw.p, ctx->ws_inv.p, lv_of(p, k), zl, md);
+                           return fs->zpass(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                                            std::max(ch.max_atoms, 1), ctx->zat.p, (const int32_t *)ctx->zbt.p, rs,
+                                            ctx->tw.p, ctx->ws_inv.p, lv_of(p, k), zl, md);
+                       }));
+                HIPCHK(ctx, timed(ctx, FFTDG_K_INV, hybrid ? 0.0 : pb * ch.pp, [&] {
+                           return fs->inv(st, occ, dinv + ch.off0, nloc, (int)ch.ninv, ccfg, ctx->ws_inv.p, beta,
+                                          ctx->tw.p, fb_of(p, k), lv_of(p, k), pp_of(s), psi_out, clash_out,
+                                          ctx->prof ? (unsigned int *)ctx->prof_cnt.p : nullptr, fc, md);
+                       }));
+                if (ctx->prof) ctx->prof_fused = true;
+            }
             if (overlap) HIPCHK(ctx, hipEventRecord(ctx->ev_main[p], st));
-            if (ctx->prof) ctx->prof_fused = true;
         }
     }
     if (overlap) {  // join: later work on `st` sees the side stream's work done
@@ -1039,7 +1052,7 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     const bool graph_ok = ctx->use_graph && !ctx->prof && !psi_out && !clash_out && out;
     if (!graph_ok) return launch_all(ctx->stream);
     std::vector<int64_t> sig = {(int64_t)(intptr_t)ks, occ, ctx->edirect, grp, s_begin, s_end, P.fused, P.fused_planes,
-                                overlap, (int64_t)(intptr_t)ctx->side,
+                                overlap, (int64_t)(intptr_t)ctx->side, sgrp,
                                 (int64_t)(intptr_t)ctx->runs.p, (int64_t)(intptr_t)ctx->run_cnt.p,
                                 (int64_t)(intptr_t)ctx->fbits.p, (int64_t)(intptr_t)ctx->lives.p,
                                 (int64_t)(intptr_t)ctx->dil.p, (int64_t)o_item, (int64_t)(intptr_t)ctx->zat.p,
