@@ -41,7 +41,8 @@ struct KernelSet {
     hipError_t (*inv)(hipStream_t, bool occ, const int32_t *inv_off, int n_cfg, int n_items, const CfgDev *cfgs,
                       const void *wsi, double beta, const void *tw, void *pp, void *psi_out,
                       uint8_t *clash_out, unsigned int *e_count);
-    hipError_t (*merge)(hipStream_t, const CfgDev *cfgs, int n_cfg, const void *pp, fftdg_partial *out);
+    hipError_t (*merge)(hipStream_t, const CfgDev *cfgs, int n_cfg, int ns, const void *pp, int64_t pp_snap,
+                        fftdg_partial *out, int64_t out_snap);
 };
 
 const KernelSet *kernel_set(int precision, int n_fft);
@@ -58,8 +59,11 @@ hipError_t launch_pair_energies(hipStream_t st, int n_rec_atoms, const double *r
                                 const double *ls, const double *le, int n_poses, const double *pose, int excl,
                                 double *out);
 
+// scratch of launch_sample_translations over n translations
+size_t sir_scratch_bytes(int64_t n);
 hipError_t launch_sample_translations(hipStream_t st, int precision, const void *psi, const uint8_t *clash, int n,
-                                     double beta, const double *u, int nu, int32_t *out_lin, double *out_psi);
+                                     double beta, const double *u, int nu, double *scratch, int32_t *out_lin,
+                                     double *out_psi);
 
 hipError_t launch_scan_features(hipStream_t st, const fftdg_partial *p, int64_t n_cfg_total, int n_snap, int n_lig,
                                 const int32_t *cfg_off, const double *W, float *feat, int ld, int col0);

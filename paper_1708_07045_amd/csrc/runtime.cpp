@@ -94,7 +94,7 @@ struct fftdg_ctx {
     DevBuf counts;                            // fused path: per-item counts of the clash test (see run_plan)
     DevBuf corners, zlist, need;              // fused path: direct energies' atoms; configurations that take the transforms
     DevBuf rgrid;                             // receptor grids [snap][3][n_rec^3] of the direct energies (fused path, OCC)
-    DevBuf sir_psi, sir_clash, sir_u, sir_lin, sir_psi_out;  // pose resampling
+    DevBuf sir_psi, sir_clash, sir_u, sir_lin, sir_psi_out, sir_seg;  // pose resampling
     int n_snap = 0;
     std::vector<double> W;
     void *pinned = nullptr;
@@ -974,13 +974,13 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         HIPCHK(ctx, hipEventRecord(ctx->ev_join, sc));
         HIPCHK(ctx, hipStreamWaitEvent(st, ctx->ev_join, 0));
     }
-    if (out)
-        for (int s = s_begin; s < s_end; ++s) {
-            const void *pp_s = (const char *)ctx->pp.p + pp_snap * (size_t)(s - s_begin);
-            HIPCHK(ctx, timed(ctx, FFTDG_K_MERGE, pb * (double)P.total_pp + sizeof(fftdg_partial) * (double)ncfg, [&] {
-                       return ks->merge(st, dcfg, ncfg, pp_s, out + (size_t)s * ncfg);
-                   }));
-        }
+    if (out) {
+        const int ns = s_end - s_begin;
+        HIPCHK(ctx, timed(ctx, FFTDG_K_MERGE, ns * (pb * (double)P.total_pp + sizeof(fftdg_partial) * (double)ncfg), [&] {
+                   return ks->merge(st, dcfg, ncfg, ns, ctx->pp.p, (int64_t)(pp_snap / ks->ppbytes),
+                                    out + (size_t)s_begin * ncfg, ncfg);
+               }));
+    }
     return FFTDG_OK;
     };
     auto launch_all = [&](hipStream_t st) -> int {
@@ -1040,13 +1040,13 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         HIPCHK(ctx, hipEventRecord(ctx->ev_join, si));
         HIPCHK(ctx, hipStreamWaitEvent(st, ctx->ev_join, 0));
     }
-    if (out)
-        for (int s = s_begin; s < s_end; ++s) {
-            const void *pp_s = (const char *)ctx->pp.p + pp_snap * (size_t)(s - s_begin);
-            HIPCHK(ctx, timed(ctx, FFTDG_K_MERGE, pb * (double)P.total_pp + sizeof(fftdg_partial) * (double)ncfg, [&] {
-                       return ks->merge(st, dcfg, ncfg, pp_s, out + (size_t)s * ncfg);
-                   }));
-        }
+    if (out) {
+        const int ns = s_end - s_begin;
+        HIPCHK(ctx, timed(ctx, FFTDG_K_MERGE, ns * (pb * (double)P.total_pp + sizeof(fftdg_partial) * (double)ncfg), [&] {
+                   return ks->merge(st, dcfg, ncfg, ns, ctx->pp.p, (int64_t)(pp_snap / ks->ppbytes),
+                                    out + (size_t)s_begin * ncfg, ncfg);
+               }));
+    }
     return FFTDG_OK;
     };
     const bool graph_ok = ctx->use_graph && !ctx->prof && !psi_out && !clash_out && out;
@@ -1246,7 +1246,7 @@ void fftdg_destroy(fftdg_ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     DevBuf *bufs[] = {&c->tw, &c->rspec, &c->rxy, &c->ws_fwd, &c->ws_inv, &c->pp, &c->tables,
                       &c->red_B, &c->red_res, &c->red_off, &c->red_W, &c->prof_cnt, &c->tune_out,
-                      &c->sir_psi, &c->sir_clash, &c->sir_u, &c->sir_lin, &c->sir_psi_out,
+                      &c->sir_psi, &c->sir_clash, &c->sir_u, &c->sir_lin, &c->sir_psi_out, &c->sir_seg,
                       &c->dil, &c->runs, &c->run_cnt, &c->fbits, &c->lives, &c->zat, &c->zbt, &c->surv,
                       &c->counts, &c->corners, &c->zlist, &c->need, &c->rgrid};
     for (DevBuf *b : bufs)
@@ -1834,13 +1834,15 @@ int fftdg_sample_poses(fftdg_ctx *ctx, const fftdg_batch *b, const fftdg_partial
         if ((rc = reserve(ctx, ctx->sir_u, sizeof(double) * uu.size()))) return rc;
         if ((rc = reserve(ctx, ctx->sir_lin, sizeof(int32_t) * uu.size()))) return rc;
         if ((rc = reserve(ctx, ctx->sir_psi_out, sizeof(double) * uu.size()))) return rc;
+        if ((rc = reserve(ctx, ctx->sir_seg, sir_scratch_bytes(n)))) return rc;
         if ((rc = run_plan(ctx, b, PL, T_K, nullptr, snap, ctx->sir_psi.p, (uint8_t *)ctx->sir_clash.p))) return rc;
         HIPCHK(ctx, hipMemcpyAsync(ctx->sir_u.p, uu.data(), sizeof(double) * uu.size(), hipMemcpyHostToDevice,
                                    ctx->stream));
         HIPCHK(ctx, launch_sample_translations(ctx->stream, ctx->g.precision, ctx->sir_psi.p,
                                                (const uint8_t *)ctx->sir_clash.p, n, beta,
                                                (const double *)ctx->sir_u.p, (int)uu.size(),
-                                               (int32_t *)ctx->sir_lin.p, (double *)ctx->sir_psi_out.p));
+                                               (double *)ctx->sir_seg.p, (int32_t *)ctx->sir_lin.p,
+                                               (double *)ctx->sir_psi_out.p));
         lin.resize(uu.size());
         ps.resize(uu.size());
         HIPCHK(ctx, hipMemcpyAsync(lin.data(), ctx->sir_lin.p, sizeof(int32_t) * uu.size(), hipMemcpyDeviceToHost,

@@ -300,13 +300,9 @@ struct LseAcc {
     }
 };
 
-// Workgroup reduction of the per-thread partials in a fixed tree: a
-// butterfly over the lanes of each wavefront (shuffles, no barrier), then
-// thread 0 merges the wavefronts' results in order and stores the plane
-// partial.  red holds one entry per wavefront of the NTH-thread workgroup.
-template <typename T, int NTH = NT>
-__device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red, PlanePartial<T> *out,
-                                                    int tid = threadIdx.x) {
+// Butterfly over the lanes of a wavefront: every lane gets the merge of all.
+template <typename T>
+__device__ __forceinline__ void wave_merge(LseAcc<T> &a) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         LseAcc<T> o;
@@ -317,6 +313,16 @@ __device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red,
         o.amin = __shfl_xor(a.amin, off);
         a.merge(o);
     }
+}
+
+// Workgroup reduction of the per-thread partials in a fixed tree: a
+// butterfly over the lanes of each wavefront (shuffles, no barrier), then
+// thread 0 merges the wavefronts' results in order and stores the plane
+// partial.  red holds one entry per wavefront of the NTH-thread workgroup.
+template <typename T, int NTH = NT>
+__device__ __forceinline__ void block_partial_store(LseAcc<T> a, LseAcc<T> *red, PlanePartial<T> *out,
+                                                    int tid = threadIdx.x) {
+    wave_merge(a);
     if ((tid & 63) == 0) red[tid >> 6] = a;
     __syncthreads();
     if (tid == 0) {

@@ -1360,18 +1360,24 @@ __global__ __launch_bounds__(NT) void k_inv_xy_lse(const int32_t *__restrict__ i
     block_partial_store(acc, red, pp + c.pp_base + tz);
 }
 
-// Per configuration: merge its plane partials (fixed order, working precision).
+// Per configuration: merge its plane partials (fixed order, working
+// precision), one wavefront each and a snapshot per blockIdx.y (strides of
+// the two arrays).  Latency bound: a thread per configuration walked up to
+// 128 dependent merges, 28 us for 9 configurations at 128^3 (now 5) and as
+// much again for each snapshot.
 template <typename T>
-__global__ void k_merge(const CfgDev *__restrict__ cfgs, int n_cfg, const PlanePartial<T> *__restrict__ pp,
-                        fftdg_partial *__restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(NT) void k_merge(const CfgDev *__restrict__ cfgs, int n_cfg,
+                                               const PlanePartial<T> *__restrict__ pp, int64_t pp_snap,
+                                               fftdg_partial *__restrict__ out, int64_t out_snap) {
+    const int i = (int)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (i >= n_cfg) return;
-    const CfgDev c = cfgs[i];
+    const CfgDev &c = cfgs[i];
     LseAcc<T> a;
     a.init();
     if (c.scanned) {
-        for (int tz = 0; tz < c.V[2]; ++tz) {
-            const PlanePartial<T> p = pp[c.pp_base + tz];
+        const PlanePartial<T> *q = pp + blockIdx.y * pp_snap + c.pp_base;
+        for (int tz = threadIdx.x & 63; tz < c.V[2]; tz += 64) {
+            const PlanePartial<T> p = q[tz];
             LseAcc<T> b;
             b.m = p.m;
             b.s = p.s;
@@ -1380,7 +1386,9 @@ __global__ void k_merge(const CfgDev *__restrict__ cfgs, int n_cfg, const PlaneP
             b.amin = p.argmin;
             a.merge(b);
         }
+        wave_merge(a);
     }
+    if ((threadIdx.x & 63) != 0) return;
     fftdg_partial o;
     o.m = (double)a.m;
     o.s = (double)a.s;
@@ -1389,7 +1397,7 @@ __global__ void k_merge(const CfgDev *__restrict__ cfgs, int n_cfg, const PlaneP
     o.n_finite = a.n;
     o.argmin = a.amin;
     o.scanned = c.scanned;
-    out[c.global_cfg] = o;
+    out[blockIdx.y * out_snap + c.global_cfg] = o;
 }
 
 // FP64 exponential averages per ligand (one workgroup per ligand).
@@ -1761,66 +1769,151 @@ __global__ __launch_bounds__(NT) void k_scan_features(const fftdg_partial *__res
 }
 
 // Translation draws of sampling importance resampling for one
-// configuration (one block): weights w_i = exp(-beta (Psi_i - Psi_min)) over
-// the clash-free translations i of the exported grid (linear order
-// (tz, ty, tx)), FP64; draw j takes the first i whose running sum of w
-// exceeds u_j times the total.  Each thread owns a contiguous segment; a
-// draw finds its segment from the segments' running sums, then scans it.
+// configuration: weights w_i = exp(-beta (Psi_i - Psi_min)) over the
+// clash-free translations i of the exported grid (linear order (tz, ty, tx)),
+// FP64; draw j takes the first i whose running sum of w exceeds u_j times
+// the total.  Segments of SIR_SEG translations: k_sir_min their minima,
+// k_sir_sum their weights' sums, k_sir_draw one block per draw, which finds
+// its segment from the segments' running sums, then its place in it.
+// One block over the whole grid took 500 us at 90^3 translations (512
+// dependent strided loads and two exponentials each); these three 18 us
+// together, 5 to 7 each: launches and one pass over the grid.
+constexpr int SIR_PER = 8, SIR_SEG = SIR_PER * NT;
+
+// exclusive running sums over the block; sh: one entry per wavefront and one
+// for the total
+__device__ __forceinline__ double block_excl_sum(double v, double *sh, double &total) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    double e = __shfl_up(x, 1);
+    if (lane == 0) e = 0.0;
+    __syncthreads();
+    if (lane == 63) sh[wv] = x;
+    __syncthreads();
+    total = 0.0;
+    double base = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+        if (w == wv) base = total;
+        total += sh[w];
+    }
+    return base + e;
+}
+
+__device__ __forceinline__ double block_min(double v, double *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(v, off);
+        v = o < v ? o : v;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = sh[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) v = sh[w] < v ? sh[w] : v;
+    return v;
+}
+
 template <typename T>
-__global__ __launch_bounds__(NT) void k_sample_translations(const T *__restrict__ psi,
-                                                            const uint8_t *__restrict__ clash, int n, double beta,
-                                                            const double *__restrict__ u, int nu,
-                                                            int32_t *__restrict__ out_lin, double *__restrict__ out_psi) {
-    __shared__ double seg[NT + 1];
-    __shared__ double red[NT];
-    const int t = threadIdx.x;
-    const int L = (n + NT - 1) / NT;
-    const int a = min(n, t * L), e = min(n, a + L);
+__global__ __launch_bounds__(NT) void k_sir_min(const T *__restrict__ psi, const uint8_t *__restrict__ clash, int n,
+                                                 double *__restrict__ seg_min) {
+    __shared__ double sh[NT / 64];
     double pm = INFINITY;
-    for (int i = a; i < e; ++i)
-        if (!clash[i] && (double)psi[i] < pm) pm = (double)psi[i];
-    red[t] = pm;
-    __syncthreads();
-    for (int w = NT / 2; w > 0; w >>= 1) {
-        if (t < w) red[t] = red[t] < red[t + w] ? red[t] : red[t + w];
-        __syncthreads();
+    for (int k = 0; k < SIR_PER; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * SIR_SEG + k * NT + threadIdx.x;
+        if (i < n && !clash[i] && (double)psi[i] < pm) pm = (double)psi[i];
     }
-    const double P0 = red[0];
-    double sum = 0.0;
-    for (int i = a; i < e; ++i)
-        if (!clash[i]) sum += exp(-beta * ((double)psi[i] - P0));
-    seg[t + 1] = sum;
+    pm = block_min(pm, sh);
+    if (threadIdx.x == 0) seg_min[blockIdx.x] = pm;
+}
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_sir_sum(const T *__restrict__ psi, const uint8_t *__restrict__ clash, int n,
+                                                 double beta, const double *__restrict__ seg_min,
+                                                 double *__restrict__ seg_sum, double *__restrict__ psi_min) {
+    __shared__ double sh[NT / 64];
+    double pm = INFINITY;
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += NT) pm = seg_min[k] < pm ? seg_min[k] : pm;
+    pm = block_min(pm, sh);
+    double sum = 0.0, total;
+    for (int k = 0; k < SIR_PER; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * SIR_SEG + k * NT + threadIdx.x;
+        if (i < n && !clash[i]) sum += exp(-beta * ((double)psi[i] - pm));
+    }
+    (void)block_excl_sum(sum, sh, total);
+    if (threadIdx.x == 0) seg_sum[blockIdx.x] = total;
+    if (threadIdx.x == 0 && blockIdx.x == 0) *psi_min = pm;
+}
+
+// Largest k in [0, n) with pre[k] <= x (0 if none).
+__device__ __forceinline__ int last_not_above(const double *pre, int n, double x) {
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pre[mid] <= x) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_sir_draw(const T *__restrict__ psi, const uint8_t *__restrict__ clash, int n,
+                                                  double beta, int n_seg, const double *__restrict__ seg_sum,
+                                                  const double *__restrict__ psi_min, const double *__restrict__ u,
+                                                  int32_t *__restrict__ out_lin, double *__restrict__ out_psi) {
+    __shared__ double pre[NT], sh[NT / 64], sseg[2];
+    const int t = threadIdx.x, j = blockIdx.x;
+    const double P0 = *psi_min;
+    // running sums over the threads' shares of the segments
+    const int per = (n_seg + NT - 1) / NT, k0 = min(n_seg, t * per), k1 = min(n_seg, k0 + per);
+    double v = 0.0, total;
+    for (int k = k0; k < k1; ++k) v += seg_sum[k];
+    pre[t] = block_excl_sum(v, sh, total);
     __syncthreads();
+    const double x = u[j] * total;
     if (t == 0) {
-        seg[0] = 0.0;
-        for (int k = 1; k <= NT; ++k) seg[k] += seg[k - 1];
+        const int w = last_not_above(pre, NT, x);
+        double run = pre[w];
+        int k = min(w * per, n_seg - 1);
+        for (; k < min(n_seg, w * per + per) - 1; ++k) {
+            if (run + seg_sum[k] > x) break;
+            run += seg_sum[k];
+        }
+        sseg[0] = (double)k;
+        sseg[1] = run;
     }
     __syncthreads();
-    const double total = seg[NT];
-    for (int j = t; j < nu; j += NT) {
-        const double x = u[j] * total;
-        // segment k: seg[k] <= x < seg[k + 1]
-        int lo = 0, hi = NT;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (seg[mid] <= x) lo = mid; else hi = mid;
-        }
-        const int sa = min(n, lo * L), se = min(n, sa + L);
-        double run = seg[lo];
-        int pick = -1;
-        for (int i = sa; i < se; ++i) {
-            if (clash[i]) continue;
-            run += exp(-beta * ((double)psi[i] - P0));
-            pick = i;
-            if (run > x) break;
-        }
-        if (pick < 0) {  // x at the very top: the last clash-free translation
-            for (int i = n - 1; i >= 0; --i)
-                if (!clash[i]) { pick = i; break; }
-        }
-        out_lin[j] = pick;
-        out_psi[j] = (double)psi[pick];
+    const int64_t i0 = (int64_t)sseg[0] * SIR_SEG + t * SIR_PER;
+    const double before = sseg[1];
+    double wt[SIR_PER];
+    v = 0.0;
+#pragma unroll
+    for (int k = 0; k < SIR_PER; ++k) {
+        const bool ok = i0 + k < n && !clash[i0 + k];
+        wt[k] = ok ? exp(-beta * ((double)psi[i0 + k] - P0)) : -1.0;
+        v += ok ? wt[k] : 0.0;
     }
+    pre[t] = before + block_excl_sum(v, sh, total);
+    __syncthreads();
+    if (t != last_not_above(pre, NT, x)) return;
+    double run = pre[t];
+    int64_t pick = -1;
+#pragma unroll
+    for (int k = 0; k < SIR_PER; ++k) {
+        if (wt[k] < 0.0 || run > x) continue;
+        run += wt[k];
+        pick = i0 + k;
+    }
+    // none here: x at the very top (or a running sum's last bit)
+    for (int64_t i = min(i0, (int64_t)n) - 1; pick < 0 && i >= 0; --i)
+        if (!clash[i]) pick = i;
+    out_lin[j] = (int32_t)pick;
+    out_psi[j] = pick < 0 ? (double)INFINITY : (double)psi[pick];
 }
 
 // Interaction energy of ligand poses from the receptor grids by trilinear
@@ -2193,10 +2286,13 @@ struct Launch {
                                e_count);
         return hipGetLastError();
     }
-    static hipError_t merge(hipStream_t st, const CfgDev *cfgs, int n_cfg, const void *pp, fftdg_partial *out) {
+    static hipError_t merge(hipStream_t st, const CfgDev *cfgs, int n_cfg, int ns, const void *pp, int64_t pp_snap,
+                            fftdg_partial *out, int64_t out_snap) {
         if (n_cfg <= 0) return hipSuccess;
-        hipLaunchKernelGGL((k_merge<T>), dim3((n_cfg + 127) / 128), dim3(128), 0, st, cfgs, n_cfg,
-                           (const PlanePartial<T> *)pp, out);
+        for (int s = 0; s < ns; s += 65535)  // grid.y
+            hipLaunchKernelGGL((k_merge<T>), dim3((n_cfg + NT / 64 - 1) / (NT / 64), ns - s < 65535 ? ns - s : 65535),
+                               dim3(NT), 0, st, cfgs, n_cfg, (const PlanePartial<T> *)pp + s * pp_snap, pp_snap,
+                               out + s * out_snap, out_snap);
         return hipGetLastError();
     }
 };
@@ -2327,14 +2423,26 @@ hipError_t launch_pair_energies(hipStream_t st, int n_rec_atoms, const double *r
     return hipGetLastError();
 }
 
+size_t sir_scratch_bytes(int64_t n) { return sizeof(double) * (size_t)(2 * ((n + SIR_SEG - 1) / SIR_SEG) + 1); }
+
+template <typename T>
+static void sample_translations(hipStream_t st, const T *psi, const uint8_t *clash, int n, double beta,
+                                const double *u, int nu, double *scratch, int32_t *out_lin, double *out_psi) {
+    const int ns = (int)(((int64_t)n + SIR_SEG - 1) / SIR_SEG);
+    double *mn = scratch, *sum = scratch + ns, *p0 = scratch + 2 * ns;
+    hipLaunchKernelGGL((k_sir_min<T>), dim3(ns), dim3(NT), 0, st, psi, clash, n, mn);
+    hipLaunchKernelGGL((k_sir_sum<T>), dim3(ns), dim3(NT), 0, st, psi, clash, n, beta, mn, sum, p0);
+    hipLaunchKernelGGL((k_sir_draw<T>), dim3(nu), dim3(NT), 0, st, psi, clash, n, beta, ns, sum, p0, u, out_lin,
+                       out_psi);
+}
+
 hipError_t launch_sample_translations(hipStream_t st, int precision, const void *psi, const uint8_t *clash, int n,
-                                     double beta, const double *u, int nu, int32_t *out_lin, double *out_psi) {
+                                     double beta, const double *u, int nu, double *scratch, int32_t *out_lin,
+                                     double *out_psi) {
     if (precision == FFTDG_F64)
-        hipLaunchKernelGGL((k_sample_translations<double>), dim3(1), dim3(NT), 0, st, (const double *)psi, clash, n,
-                           beta, u, nu, out_lin, out_psi);
+        sample_translations(st, (const double *)psi, clash, n, beta, u, nu, scratch, out_lin, out_psi);
     else
-        hipLaunchKernelGGL((k_sample_translations<float>), dim3(1), dim3(NT), 0, st, (const float *)psi, clash, n,
-                           beta, u, nu, out_lin, out_psi);
+        sample_translations(st, (const float *)psi, clash, n, beta, u, nu, scratch, out_lin, out_psi);
     return hipGetLastError();
 }
 
