@@ -87,7 +87,7 @@ struct FusedSet {
     // configurations go through the transforms (zlist, need, out[2] as
     // k_modes writes them; done: one int per configuration, zero at the
     // chunk's start); Eq. 2 plane partials of the others from the receptor
-    // grids [3][n_rec^3].  ns snapshots a launch; need and out[1] are for all
+    // grids (grid_points).  ns snapshots a launch; need and out[1] are for all
     // of them together
     size_t corner_bytes;
     hipError_t (*corner_atoms)(hipStream_t, const CfgDev *cfgs, const int32_t *zcfg, int nz, int max_atoms,
@@ -97,6 +97,8 @@ struct FusedSet {
     hipError_t (*direct)(hipStream_t, int ns, const SnapStride &st, const int32_t *inv_off, int n_cfg, int n_items,
                          const CfgDev *cfgs, const void *atoms, int max_atoms, const void *grids, int n_rec,
                          double beta, const uint32_t *fb, const uint8_t *live, const int32_t *fcnt, void *pp);
+    // a snapshot's receptor grids [3][n_rec^3] in the layout direct reads, [n_rec^3][3]
+    hipError_t (*grid_points)(hipStream_t, const void *grids, int n_rec, void *out);
     // per scanned configuration of a chunk: its atoms sorted by plane with
     // their x/y placement and channel weights, and the plane starts
     // (zat: nz x max_atoms records, zbt: nz x (N + 2) ints)

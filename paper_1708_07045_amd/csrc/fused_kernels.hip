@@ -596,11 +596,11 @@ __global__ void k_zero32(int32_t *__restrict__ p, int n) {
 // the device once the clash test is done; a configuration with more than
 // direct_pairs goes through the transforms, listed by k_modes.  The lines lie
 // where the two cost the same (one stream, us per configuration): N = 128,
-// FP32: 7.3 ns per 1000 pairs (347 k pairs: 2.5 us) against 7.1-8.4 us of
+// FP32: 5.5 ns per 1000 pairs (347 k pairs: 1.9 us) against 7.1-8.4 us of
 // transforms; N = 64: 12 ns per 1000 pairs against 1.15 us in FP32, 13 ns
 // against 2.3 us in FP64; N = 32: some 13 ns against 0.27 and 0.43 us.
 // 8000 site configurations (25 atoms, 3 % of the translations free, 160 k
-// pairs each): 46.0 ms of forward planes, z pass and inverse -> 6.9 ms.
+// pairs each): 46.0 ms of forward planes, z pass and inverse -> 5.2 ms.
 template <typename T, int N>
 __host__ __device__ constexpr long long direct_pairs() {
     return N == 128 ? 1000000 : (N == 64 ? (sizeof(T) == 8 ? 150000 : 100000) : (sizeof(T) == 8 ? 30000 : 20000));
@@ -611,8 +611,8 @@ __device__ __forceinline__ bool by_transforms(int n_free, int n_atoms) {
 }
 
 // A placed atom of a scanned configuration as k_direct reads it (by scalar
-// loads): byte offset of its first corner in one channel's grid, and the
-// weight of corner (dz, dy, dx) for channel ch at [(2 dz + dy) 6 + 2 ch + dx].
+// loads): byte offset of its first corner's point, and the weight of corner
+// (dz, dy, dx) for channel ch at [(2 dz + dy) 6 + 3 dx + ch].
 template <typename T>
 struct alignas(16) CornerAtom {
     int32_t off;
@@ -638,14 +638,14 @@ __global__ __launch_bounds__(NT) void k_corner_atoms(const CfgDev *__restrict__ 
         f[d][0] = 1.0 - f[d][1];
     }
     CornerAtom<T> r;
-    r.off = (((U[2] >> 16) * n_rec + (U[1] >> 16)) * n_rec + (U[0] >> 16)) * (int)sizeof(T);
+    r.off = (((U[2] >> 16) * n_rec + (U[1] >> 16)) * n_rec + (U[0] >> 16)) * 3 * (int)sizeof(T);
     r.pad[0] = r.pad[1] = r.pad[2] = 0;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
         const double g = (double)gam[3 * (c.atom_base + a) + ch];
 #pragma unroll
         for (int k = 0; k < 8; ++k)  // k = 4 dz + 2 dy + dx; rounded once
-            r.w[(k >> 1) * 6 + 2 * ch + (k & 1)] = (T)(f[2][k >> 2] * f[1][(k >> 1) & 1] * f[0][k & 1] * g);
+            r.w[(k >> 1) * 6 + 3 * (k & 1) + ch] = (T)(f[2][k >> 2] * f[1][(k >> 1) & 1] * f[0][k & 1] * g);
     }
     out[(int64_t)zi * ma + a] = r;
 }
@@ -684,12 +684,38 @@ __global__ __launch_bounds__(NT) void k_modes(const CfgDev *__restrict__ cfgs, c
     if (threadIdx.x == 0) out[1] = nneed;
 }
 
+// Receptor grids [3][n^3] as k_direct reads them, a point's three channels
+// side by side.
+template <typename T>
+__global__ __launch_bounds__(NT) void k_grid_points(const T *__restrict__ grids, int64_t n3, T *__restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (i >= n3) return;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) out[3 * i + ch] = grids[ch * n3 + i];
+}
+
+// Points x and x + 1 of a row: 6 values
+__device__ __forceinline__ void load_pair(__amdgpu_buffer_rsrc_t r, int vo, int so, float *v) {
+    const float4 a = buf_load4(r, vo, so);
+    const float2 b = buf_load(r, vo + 16, so, (float2 *)nullptr);
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y;
+}
+__device__ __forceinline__ void load_pair(__amdgpu_buffer_rsrc_t r, int vo, int so, double *v) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double2 a = buf_load(r, vo + 16 * k, so, (double2 *)nullptr);
+        v[2 * k] = a.x, v[2 * k + 1] = a.y;
+    }
+}
+
 // One block per (configuration, box-valid z-translation): the plane's free
 // translations, in order of their linear index, one per thread; a wavefront
-// walks the configuration's atoms, whose corners come as 12 loads of an
-// x-adjacent pair (3 channels x 4 rows) at the lane's translation plus an
-// offset in an SGPR, and whose 24 weights are scalar operands.  Bound: the
-// loads' way through L1 (96 bytes per pair of translation and atom).
+// walks the configuration's atoms, whose corners come as four times six
+// values (two points along x, three channels each) at the lane's translation
+// plus an offset in an SGPR, and whose 24 weights are scalar operands.
+// Bound: the loads' way through L1, 96 bytes per pair of translation and
+// atom, and the lines that feed it (with a grid per channel these were
+// twice as many: 8000 site configurations 6.9 -> 5.2 ms).
 template <int N>
 __host__ __device__ constexpr int direct_threads() {
     return N == 128 ? 256 : 64;
@@ -705,7 +731,6 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
     constexpr int ND = direct_threads<N>(), NW = N / 32;
     constexpr int MAXW = N * NW;                   // words of a plane's free bits
     constexpr int PER = (MAXW + ND - 1) / ND;
-    using T2 = typename Cx<T>::t;
     __shared__ int pre[PER * ND + 1];              // free translations before each word
     __shared__ int sh[ND / 64];
     __shared__ LseAcc<T> red[ND / 64];
@@ -762,9 +787,8 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
         base += cnt[k];
     }
     __syncthreads();
-    const int row = n_rec * (int)sizeof(T), plane = n_rec * row;
-    const int chan = n_rec * plane;
-    const auto rs = make_rsrc(grids, 3 * chan);
+    const int row = n_rec * 3 * (int)sizeof(T), plane = n_rec * row;
+    const auto rs = make_rsrc(grids, n_rec * plane);
     const CornerAtom<T> *__restrict__ A = atoms + (int64_t)c.zrow * ma;
     for (int j = threadIdx.x; j < F; j += ND) {
         // word holding free translation j, then its (j - pre)-th set bit
@@ -776,20 +800,20 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
         uint32_t b = fp[lo];
         for (int k = j - pre[lo]; k > 0; --k) b &= b - 1u;
         const int ty = lo / W, tx = 32 * (lo - (lo / W) * W) + __builtin_ctz(b);
-        const int vo = ((tz * n_rec + ty) * n_rec + tx) * (int)sizeof(T);
+        const int vo = ((tz * n_rec + ty) * n_rec + tx) * 3 * (int)sizeof(T);
+        constexpr int UNR = sizeof(T) == 8 ? 1 : 2;  // atoms in flight: 89 and 68 registers
         double sum = 0.0;  // over atoms in FP64: two instructions beside an atom's 24
-#pragma unroll 2
+#pragma unroll UNR
         for (int a = 0; a < n_atoms; ++a) {
             const int off = A[a].off;
             T e[2] = {(T)0, (T)0};
 #pragma unroll
-            for (int p = 0; p < 4; ++p)
+            for (int p = 0; p < 4; ++p) {
+                T v[6];
+                load_pair(rs, vo, off + (p >> 1) * plane + (p & 1) * row, v);
 #pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const T2 v = buf_load(rs, vo, off + ch * chan + (p >> 1) * plane + (p & 1) * row, (T2 *)nullptr);
-                    e[0] += A[a].w[6 * p + 2 * ch] * v.x;
-                    e[1] += A[a].w[6 * p + 2 * ch + 1] * v.y;
-                }
+                for (int k = 0; k < 6; ++k) e[k / 3] += A[a].w[6 * p + k] * v[k];
+            }
             sum += (double)(e[0] + e[1]);
         }
         const T psi = (T)sum;
@@ -1394,6 +1418,12 @@ struct LaunchFused {
                            (PlanePartial<T> *)pp, ss);
         return hipGetLastError();
     }
+    static hipError_t grid_points(hipStream_t st, const void *grids, int n_rec, void *out) {
+        const int64_t n3 = (int64_t)n_rec * n_rec * n_rec;
+        hipLaunchKernelGGL((k_grid_points<T>), dim3((unsigned)((n3 + NT - 1) / NT)), dim3(NT), 0, st, (const T *)grids,
+                           n3, (T *)out);
+        return hipGetLastError();
+    }
     static int atoms_per_table() {
         constexpr int FP = G::U + 1;
         int a = (int)(FUSED_TABLE_BYTES / (FP * sizeof(C2)));
@@ -1488,6 +1518,7 @@ static const FusedSet *make_fused() {
         LaunchFused<T, N>::corner_atoms,
         LaunchFused<T, N>::modes,
         LaunchFused<T, N>::direct,
+        LaunchFused<T, N>::grid_points,
         LaunchFused<T, N>::zprep,
         sizeof(ZAtom<T>),
         LaunchFused<T, N>::zpass,

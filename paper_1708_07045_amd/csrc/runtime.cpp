@@ -90,10 +90,10 @@ struct fftdg_ctx {
     DevBuf tw, rspec, rxy, ws_fwd, ws_inv, pp, tables, red_B, red_res, red_off, red_W;
     DevBuf dil, runs, run_cnt, fbits, lives;  // fused path: receptor bit rows, ligand runs, clash results
     DevBuf zat, zbt;                          // fused path: sorted atoms and plane starts per configuration
-    DevBuf surv;                              // fused path: undecided rows of the clash test
+    DevBuf surv;                              // fused path: undecided segments of the clash test
     DevBuf counts;                            // fused path: per-item counts of the clash test (see run_plan)
     DevBuf corners, zlist, need;              // fused path: direct energies' atoms; configurations that take the transforms
-    DevBuf rgrid;                             // receptor grids [snap][3][n_rec^3] of the direct energies (fused path, OCC)
+    DevBuf rgrid;                             // receptor grids [snap][n_rec^3][3] of the direct energies (fused path, OCC)
     DevBuf sir_psi, sir_clash, sir_u, sir_lin, sir_psi_out, sir_seg;  // pose resampling
     int n_snap = 0;
     std::vector<double> W;
@@ -1332,7 +1332,11 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
                    }));
         // the grids themselves, for the energies summed directly
         if ((rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
-        HIPCHK(ctx, hipMemcpyAsync(ctx->rgrid.p, grids, 3 * n3 * tsz * n_snap, hipMemcpyDeviceToDevice, ctx->stream));
+        for (int s = 0; s < n_snap; ++s)
+            HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, 6.0 * (double)(n3 * tsz), [&] {
+                       return ctx->fs->grid_points(ctx->stream, (const char *)grids + s * 3 * n3 * tsz, g.n_rec,
+                                                   (char *)ctx->rgrid.p + s * 3 * n3 * tsz);
+                   }));
     }
     ctx->n_snap = n_snap;
     ctx->W = W;
