@@ -54,7 +54,7 @@ struct SnapStride {
     int64_t dil;    // words of a receptor bit table
     int64_t fb;     // words of free bits
     int64_t live;   // bytes of live flags
-    int64_t surv;   // slots of the undecided-row lists
+    int64_t surv;   // slots of the undecided-segment lists
     int64_t counts; // ints of the counts (scnt, fcnt, out)
     int64_t zlist;  // ints of the list of configurations that take the transforms
     int64_t grid;   // elements of the receptor grids
@@ -74,8 +74,8 @@ struct FusedSet {
     // clears n ints
     hipError_t (*zero)(hipStream_t, int32_t *p, int64_t n);
     // free bits and live flags: item_off[0..n_cfg] running counts of the
-    // phase-1 items (tz, 64-row group), item2_off those of the phase-2 items
-    // (64-row slices of a configuration's undecided-row list); surv holds the
+    // phase-1 items (tz, 64-row group), item2_off those of the phase-2
+    // blocks (each takes every n-th 64 of a configuration's undecided segments); surv holds the
     // lists (at surv_off), scnt their lengths, fcnt the free translations per
     // configuration (n_cfg ints each, zero on entry); ns snapshots a launch
     hipError_t (*clash)(hipStream_t, int ns, const SnapStride &st, const int32_t *item_off, const int32_t *item2_off,

@@ -152,7 +152,7 @@ __device__ __forceinline__ bool ball_row(const RunAtom &A, int y, int z, int &xl
 // word for a translation of zero, o = 4 Dil<N>::index(k, z + M, b / 32,
 // y + M) with b = a + M (the lane adds 4 RW (t_z E + t_y)), and the two
 // window shifts, b mod 32 | ((b + len - 2^k) mod 32) << 8 | (second window
-// one word on) << 16, with 2^k <= len < 2^(k+1).  The planner keeps z, y,
+// one word on) << 16 | (len - 2^k) << 24, with 2^k <= len < 2^(k+1).  The planner keeps z, y,
 // a >= -M and the rows and words a translated run reads inside the table.
 template <int N>
 __device__ __forceinline__ uint2 pack_run(int z, int y, int a, int len) {
@@ -161,7 +161,8 @@ __device__ __forceinline__ uint2 pack_run(int z, int y, int a, int len) {
     const int k = 31 - __builtin_clz((unsigned)len);
     const int p2 = ax + len - (1 << k);
     const uint32_t off = (uint32_t)(4 * D::index(k, z + D::M, ax >> 5, y + D::M));
-    const uint32_t meta = (uint32_t)(ax & 31) | ((uint32_t)(p2 & 31) << 8) | ((uint32_t)((p2 >> 5) > (ax >> 5)) << 16);
+    const uint32_t meta = (uint32_t)(ax & 31) | ((uint32_t)(p2 & 31) << 8) | ((uint32_t)((p2 >> 5) > (ax >> 5)) << 16) |
+                          (uint32_t)(len - (1 << k)) << 24;
     return make_uint2(off, meta);
 }
 __device__ __forceinline__ int run_pieces(int len) { return (len + RUN_MAX - 1) / RUN_MAX; }
@@ -299,12 +300,13 @@ __global__ __launch_bounds__(RUN_NT) void k_lig_runs(const CfgDev *__restrict__ 
 // ------------------------------------------------------------ clash test
 // The test runs in two phases.  Phase 1: one wavefront per (configuration,
 // z-translation tz, group of 64 y-translations), lane = ty, tests the atom
-// chords and an evenly spread sample of CLASH_R1 runs; rows whose
-// translations all clash are done (no free bit), the others are appended to
-// the configuration's list of undecided rows.  Phase 2: wavefronts over each
-// configuration's list, lane = one undecided row (tz, ty), test every run.
-// Only the configurations that still have undecided rows (those near
-// clash-free translations) pay for the full run list.
+// chords and an evenly spread sample of CLASH_R1 runs.  Rows whose
+// translations all clash are done (no free bit); the bits left of the others
+// are appended to the configuration's list of undecided segments, 32
+// translations of one row each.  Phase 2: blocks over each configuration's
+// list, lane = one segment, test every run.  Only the configurations that
+// still have undecided rows (those near clash-free translations) pay for the
+// full run list, and of a row only the words that its undecided bits need.
 constexpr int CLASH_R1 = 96;      // runs of phase 1
 constexpr int CLASH_CHORDS = 32;  // of these the first so many in order, the others spread
 
@@ -326,10 +328,9 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int vo, 
     }
 }
 
-// Runs k in [k0, k1) of one wavefront: run index k itself (phase 2) or the
-// k-th of the spread sample (phase 1: the first NCH runs, the atom chords,
-// then stride S over the rest).  Lane row
-// (tzl, ty); W output words per lane; UR runs in flight (their table words
+// The first k1 runs of the phase-1 sample of one wavefront: the first NCH
+// runs, the atom chords, then stride S over the rest.  Lane row (tzl, ty);
+// W output words per lane; UR runs in flight (their table words
 // all requested before use).  Runs are at most 63 points long, so a run's
 // second window starts at most one word after its first: the words q1 ..
 // q1 + W + 1 of its row serve both.  rl, k and the run entries are
@@ -337,23 +338,19 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int vo, 
 // readfirstlane): the entries then come by scalar loads and their offset
 // travels in an SGPR.  With an offset the compiler takes for a lane value
 // every table load became a loop over the distinct offsets, 2700 cycles per
-// four runs.  Bound: the loads' way through L1 (16 bytes a lane and run).
-// 8000 site configurations (25 atoms, 96^3 in 128^3): phase 1 4.1 -> 2.0 ms,
-// phase 2 32.0 -> 5.95 ms with uniform entries, whole-row loads and the
-// runs of a row split over four wavefronts.  `share`
-// is called every few groups to exchange acc with the wavefronts that test
-// other runs of the same rows; a wavefront stops once its rows are full.
-template <int N, int W, bool SAMPLE, class Share>
-__device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr, int k0, int k1, int NCH, int S,
-                                           int tzl, int ty, bool act, uint32_t lm,
-                                           __amdgpu_buffer_rsrc_t rsrc, uint32_t *acc, Share &&share) {
+// four runs.  Bound: the loads' way through L1 (20 bytes a lane and run at
+// 70 translations a row).  8000 site configurations (25 atoms, 96^3 in
+// 128^3): 4.1 -> 2.0 ms.
+template <int N, int W>
+__device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr, int k1, int NCH, int S, int tzl,
+                                           int ty, bool act, uint32_t lm, __amdgpu_buffer_rsrc_t rsrc,
+                                           uint32_t *acc) {
     using D = Dil<N>;
     constexpr int UR = W <= 2 ? 8 : 4;
-    // phase 1: position m of the strided walk over the runs after the chords
-    int m = 0;
+    int m = 0;  // position of the strided walk over the runs after the chords
     const int R = nr - NCH;
     auto run_index = [&](int k) {
-        if (!SAMPLE || k < NCH) return k;
+        if (k < NCH) return k;
         const int i = NCH + m;
         m += S;
         if (m >= R) m -= R;
@@ -373,7 +370,7 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const unsigned sh1 = meta[u] & 31u, sh2 = (meta[u] >> 8) & 31u;
-            const bool hi2 = (meta[u] >> 16) != 0u;
+            const bool hi2 = (meta[u] & 0x10000u) != 0u;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 const uint32_t o1 = __builtin_amdgcn_alignbit(v[u][w + 1], v[u][w], sh1);
@@ -388,16 +385,7 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
         for (int w = 0; w < W; ++w) full = full && ((w == W - 1) ? ((acc[w] & lm) == lm) : (acc[w] == ~0u));
         return __all(!act || full) != 0;
     };
-    int k = k0;
-    if (!SAMPLE && k1 - k0 >= UR) {
-        // the last group starts early enough to be whole: a run tested twice is harmless
-        for (int g = 0; k < k1; k += UR, ++g) {
-            test(std::integral_constant<int, UR>{}, min(k, k1 - UR));
-            if ((g & 3) == 3) share(acc);
-            if (all_full()) return;
-        }
-        return;
-    }
+    int k = 0;
     for (; k + UR <= k1; k += UR) {
         test(std::integral_constant<int, UR>{}, k);
         if (all_full()) return;
@@ -405,13 +393,11 @@ __device__ __forceinline__ void clash_runs(const uint2 *__restrict__ rl, int nr,
     for (; k < k1; ++k) test(std::integral_constant<int, 1>{}, k);
 }
 
-template <int N, bool SAMPLE, class Share>
-__device__ __forceinline__ void clash_dispatch(int W, const uint2 *rl, int nr, int k0, int k1, int NCH, int S,
-                                               int tzl, int ty, bool act, uint32_t lm,
-                                               __amdgpu_buffer_rsrc_t rsrc, uint32_t *acc, Share &&share) {
+template <int N>
+__device__ __forceinline__ void clash_dispatch(int W, const uint2 *rl, int nr, int k1, int NCH, int S, int tzl, int ty,
+                                               bool act, uint32_t lm, __amdgpu_buffer_rsrc_t rsrc, uint32_t *acc) {
     constexpr int NW = N / 32;
-#define FFTDG_RUNS(WW) \
-    clash_runs<N, WW, SAMPLE>(rl, nr, k0, k1, NCH, S, tzl, ty, act, lm, rsrc, acc, share)
+#define FFTDG_RUNS(WW) clash_runs<N, WW>(rl, nr, k1, NCH, S, tzl, ty, act, lm, rsrc, acc)
     switch (W) {  // wave-uniform
     case 1: FFTDG_RUNS(1); break;
     case 2: if constexpr (NW >= 2) FFTDG_RUNS(2); break;
@@ -429,14 +415,15 @@ __device__ __forceinline__ void wave_count(int n, int lane, int32_t *total) {
     if (lane == 0 && n) atomicAdd(total, n);
 }
 
-// Phase 1.  Free bits (box-valid and clash-free) of a decided row (tz, ty)
-// go to fb[free_off + (tz Vy + ty) W + w], W = ceil(Vx / 32), bit tx & 31 of
-// word tx >> 5; an undecided row leaves its clash bits so far there and is
-// appended to the list at surv_off as (tz << 16 | ty), scnt[local config]
-// counting.  live[item_base + tz ny + g] = 1 iff the group has a free bit
-// once decided (0 until phase 2 decides its undecided rows).  fcnt[local
-// config] counts the free translations of both phases (scnt and fcnt start
-// at zero).
+// Phase 1.  Bits (box-valid and not found to clash) of row (tz, ty) go to
+// fb[free_off + (tz Vy + ty) W + w], W = ceil(Vx / 32), bit tx & 31 of word
+// tx >> 5: final where every run was tested.  Otherwise the row's bits are
+// cut, from the lowest on, into segments of 32 translations, and each is
+// appended to the list at surv_off as (tz << 16 | ty << 8 | first tx),
+// scnt[local config] counting.  live[item_base + tz ny + g] = 1 iff the group
+// has a free bit once decided (0 until phase 2 decides its segments).
+// fcnt[local config] counts the free translations of both phases (scnt and
+// fcnt start at zero).
 template <int N>
 __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_off, int n_cfg, int n_items,
                                                 const CfgDev *__restrict__ cfgs, const uint32_t *__restrict__ runs,
@@ -474,48 +461,55 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     // a stride of 1 there mends it and changes those ligands' results
     const int S = max(1, (nr - NCH) * 618 / 1000) % max(1, nr - NCH);
     const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
-    clash_dispatch<N, true>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, 0, k1, NCH, S, tz, ty, act, lm,
-                            rsrc, acc, [](uint32_t *) {});
+    clash_dispatch<N>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, k1, NCH, S, tz, ty, act, lm, rsrc, acc);
     const bool final = k1 == nr;  // every run tested: the row is decided either way
-    bool full = true, any = false;
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-        if (w < W) {
-            const uint32_t f = ~acc[w] & (w == W - 1 ? lm : ~0u);
-            full = full && f == 0u;
-        }
+    uint32_t f[NW];
+    bool any = false;
     int nfree = 0;
-    if (act) {
-        uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W;
+    uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W;
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
-            if (w < W) {
-                const uint32_t f = ~acc[w] & (w == W - 1 ? lm : ~0u);
-                o[w] = (final || full) ? f : acc[w];
-                any = any || f != 0u;
-                nfree += __popc(f);
+    for (int w = 0; w < NW; ++w) {
+        f[w] = act && w < W ? ~acc[w] & (w == W - 1 ? lm : ~0u) : 0u;
+        if (act && w < W) o[w] = f[w];
+        any = any || f[w] != 0u;
+        nfree += __popc(f[w]);
+    }
+    if (!final && __any(any))
+        for (int r = 0; r < NW; ++r) {  // segment r of every row that has one
+            int p = -1;
+#pragma unroll
+            for (int w = NW - 1; w >= 0; --w)
+                if (f[w]) p = 32 * w + __builtin_ctz(f[w]);
+            const unsigned long long um = __ballot(p >= 0);
+            if (!um) break;
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&scnt[ic], __popcll(um));
+            base = __shfl(base, 0);
+            if (p < 0) continue;
+            surv[c.surv_off + base + __popcll(um & ((1ull << lane) - 1ull))] =
+                ((uint32_t)tz << 16) | ((uint32_t)ty << 8) | (uint32_t)p;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {  // bits below p + 32 are done
+                const int d = p + 32 - 32 * w;
+                f[w] = d >= 32 ? 0u : (d > 0 ? f[w] & (~0u << d) : f[w]);
             }
-    }
-    const bool und = act && !full && !final;
-    const unsigned long long um = __ballot(und);
-    if (um) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&scnt[ic], __popcll(um));
-        base = __shfl(base, 0);
-        if (und) surv[c.surv_off + base + __popcll(um & ((1ull << lane) - 1ull))] = ((uint32_t)tz << 16) | (uint32_t)ty;
-    }
+        }
     const unsigned long long bal = __ballot(final && any);
     if (lane == 0) live[c.item_base + loc] = bal != 0ull ? 1 : 0;
     if (bal) wave_count(nfree, lane, fcnt + ic);
 }
 
-// Phase 2: block (configuration, w) takes undecided rows [64 w, 64 w + 64) of
-// the configuration's list; its wavefronts test a quarter of the runs each,
-// in interleaved groups, and exchange what they found through LDS.  A row
-// with a free bit has to meet every run (about 1550 at the site), and one
+// Phase 2: a configuration's blocks go over its list of undecided segments,
+// 64 at a time, one per lane; a block's wavefronts test a quarter of the runs
+// each and exchange what they found through LDS.  A segment with a free
+// translation has to meet every run (about 1550 at the site), and one
 // wavefront walking them alone was a chain of some 350 us even on an idle
 // chip; a chunk of 256 configurations has about 3000 such wavefronts for the
-// 8192 places the chip has, so the quarters also fill it.
+// 8192 places the chip has, so the quarters also fill it.  A lane reads
+// three words per run, at the word of its own first translation, and takes
+// both windows from them.  Bound: the loads' way through L1 (12 bytes a lane
+// and run).  8000 site configurations (25 atoms, 96^3 in 128^3): 32.0 ->
+// 4.5 ms (5.95 with a lane to a whole row and its five words).
 template <int N>
 __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2_off, int n_cfg, int n_items,
                                                 const CfgDev *__restrict__ cfgs, const uint32_t *__restrict__ runs,
@@ -527,58 +521,82 @@ __global__ __launch_bounds__(NT) void k_clash2(const int32_t *__restrict__ item2
     using D = Dil<N>;
     dil += blockIdx.y * st.dil, fb += blockIdx.y * st.fb, live += blockIdx.y * st.live;
     surv += blockIdx.y * st.surv, scnt += blockIdx.y * st.counts, fcnt += blockIdx.y * st.counts;
-    constexpr int NW = D::NW, NWV = NT / 64;
-    __shared__ uint32_t sacc[NW][64];
-    const int item = (int)blockIdx.x;
-    const int ic = find_cfg(item2_off, n_cfg, item);
-    const int wv = item - item2_off[ic];
+    constexpr int NWV = NT / 64, UR = 8;
+    __shared__ uint32_t sacc[64];
+    const int ic = find_cfg(item2_off, n_cfg, (int)blockIdx.x);
+    const int nblk = item2_off[ic + 1] - item2_off[ic];
     const int cnt = scnt[ic];
-    if (64 * wv >= cnt) return;  // block-uniform
     const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const CfgDev c = cfgs[ic];
+    const CfgDev &c = cfgs[ic];
     const int Vx = c.V[0], Vy = c.V[1];
     const int ny = (Vy + 63) >> 6;
-    const int idx = 64 * wv + lane;
-    const bool act = idx < cnt;
-    const uint32_t ent = act ? surv[c.surv_off + idx] : 0u;
-    const int tz = (int)(ent >> 16), ty = (int)(ent & 0xffffu);
     const int W = (Vx + 31) >> 5;
-    const uint32_t lm = (Vx & 31) ? ((1u << (Vx & 31)) - 1u) : ~0u;
-    uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W;
-    uint32_t acc[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        acc[w] = (act && w < W) ? o[w] : 0u;
-        if (part == 0) sacc[w][lane] = acc[w];
-    }
-    __syncthreads();
-    // clash bits only ever get set, so wavefronts may exchange them unordered
-    auto share = [&](uint32_t *a) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-            if (w < W) a[w] |= atomicOr(&sacc[w][lane], a[w]);
-    };
     const int nr = run_count[ic];
     const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
+    const uint2 *__restrict__ rl = reinterpret_cast<const uint2 *>(runs) + c.run_off;
     // this wavefront's quarter of the runs after the chords, which phase 1 tested
     const int n0 = min(nr, CLASH_CHORDS), nq = nr - n0;
-    clash_dispatch<N, false>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, n0 + nq * part / NWV,
-                             n0 + nq * (part + 1) / NWV, 0, 1, tz, ty, act, lm, rsrc, acc, share);
-    share(acc);
-    __syncthreads();
-    if (part != 0) return;
+    const int k0 = n0 + nq * part / NWV, k1 = n0 + nq * (part + 1) / NWV;
     int nfree = 0;
-    if (act) {
+    for (int wv = (int)blockIdx.x - item2_off[ic]; 64 * wv < cnt; wv += nblk) {  // block-uniform
+        const int idx = 64 * wv + lane;
+        const bool act = idx < cnt;
+        const uint32_t ent = act ? surv[c.surv_off + idx] : 0u;
+        const int tz = (int)(ent >> 16), ty = (int)(ent >> 8) & 255, first = (int)(ent & 255u);
+        // the window's words must lie in the row: the last one starts at word
+        // W - 1, its bits before `first` belong to other segments
+        const int p = min(first, 32 * (W - 1)), w0 = p >> 5, sh = p & 31;
+        uint32_t *o = fb + c.free_off + ((int64_t)tz * Vy + ty) * W + w0;
+        uint32_t cand = 0u;
+        if (part == 0) {
+            if (act) cand = ((sh ? o[1] << (32 - sh) : 0u) | o[0] >> sh) & (~0u << (first - p));
+            sacc[lane] = ~cand;
+        }
+        __syncthreads();
+        uint32_t acc = sacc[lane];
+        // clash bits only ever get set, so wavefronts may exchange them unordered
+        auto share = [&]() { acc |= atomicOr(&sacc[lane], acc); };
+        const int vo = (tz * D::E + ty) * (D::RW * 4);
+        auto test = [&](auto urc, int k) {
+            constexpr int U = decltype(urc)::value;
+            uint32_t v[U][3], meta[U];
+            int s[U];
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
-            if (w < W) {
-                const uint32_t f = ~sacc[w][lane] & (w == W - 1 ? lm : ~0u);
-                o[w] = f;
-                nfree += __popc(f);
+            for (int u = 0; u < U; ++u) {
+                const uint2 e = rl[k + u];
+                meta[u] = e.y;
+                s[u] = p + (int)(e.y & 31u);
+                load_words<3>(rsrc, vo + (s[u] >> 5) * 4, (int)e.x, v[u]);
             }
-        if (nfree) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t lo = __builtin_amdgcn_alignbit(v[u][1], v[u][0], s[u]);
+                const uint32_t hi = __builtin_amdgcn_alignbit(v[u][2], v[u][1], s[u]);
+                acc |= lo | __builtin_amdgcn_alignbit(hi, lo, meta[u] >> 24);
+            }
+        };
+        if (k1 - k0 >= UR) {
+            // the last group starts early enough to be whole: a run tested twice is harmless
+            for (int k = k0, g = 0; k < k1; k += UR, ++g) {
+                test(std::integral_constant<int, UR>{}, min(k, k1 - UR));
+                if ((g & 3) == 3) share();
+                if (__all(acc == ~0u)) break;
+            }
+        } else {
+            for (int k = k0; k < k1; ++k) test(std::integral_constant<int, 1>{}, k);
+        }
+        share();
+        __syncthreads();
+        if (part == 0 && act) {
+            const uint32_t clash = cand & sacc[lane], f = cand & ~sacc[lane];
+            // segments of a row can meet in a word: cleared by atomics
+            if (clash << sh) atomicAnd(o, ~(clash << sh));
+            if (sh && clash >> (32 - sh)) atomicAnd(o + 1, ~(clash >> (32 - sh)));
+            if (f) live[c.item_base + tz * ny + (ty >> 6)] = 1;  // same value from every writer
+            nfree += __popc(f);
+        }
     }
-    wave_count(nfree, lane, fcnt + ic);
+    if (part == 0) wave_count(nfree, lane, fcnt + ic);
 }
 
 __global__ void k_zero32(int32_t *__restrict__ p, int n) {

@@ -290,7 +290,7 @@ struct Plan {
         // fused path
         int nitems;               // clash-test items (tz, 64-row group)
         int nitems2;              // phase-2 items (64-row slices of the undecided-row lists)
-        int64_t nsurv;            // undecided-row list slots
+        int64_t nsurv;            // undecided-segment list slots
         int64_t nruns, nfree;     // run slots, free-bit words
         int max_atoms;            // most atoms of a scanned configuration
     };
@@ -572,7 +572,7 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
                     nit += d.V[2] * ny;
                     nit2 += (d.V[2] * d.V[1] + 63) / 64;
                     nfw += (int64_t)d.V[2] * d.V[1] * W;
-                    nsv += (int64_t)d.V[2] * d.V[1];
+                    nsv += (int64_t)d.V[2] * d.V[1] * W;
                     nr += d.run_cap;
                 }
                 P.zcfg.push_back(local);
