@@ -300,14 +300,14 @@ __global__ __launch_bounds__(RUN_NT) void k_lig_runs(const CfgDev *__restrict__ 
 // ------------------------------------------------------------ clash test
 // The test runs in two phases.  Phase 1: one wavefront per (configuration,
 // z-translation tz, group of 64 y-translations), lane = ty, tests the atom
-// chords and an evenly spread sample of CLASH_R1 runs.  Rows whose
+// chords and an evenly spread sample of the runs.  Rows whose
 // translations all clash are done (no free bit); the bits left of the others
 // are appended to the configuration's list of undecided segments, 32
 // translations of one row each.  Phase 2: blocks over each configuration's
 // list, lane = one segment, test every run.  Only the configurations that
 // still have undecided rows (those near clash-free translations) pay for the
 // full run list, and of a row only the words that its undecided bits need.
-constexpr int CLASH_R1 = 96;      // runs of phase 1
+constexpr int CLASH_R1 = 96;      // most runs of phase 1
 constexpr int CLASH_CHORDS = 32;  // of these the first so many in order, the others spread
 
 // K consecutive words of a table row, one or two loads
@@ -452,7 +452,12 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
 #pragma unroll
     for (int w = 0; w < NW; ++w) acc[w] = 0u;
     const int nr = run_count[ic];
-    const int k1 = min(nr, CLASH_R1);
+    // a twelfth of the runs, the chords at least: a longer sample costs every
+    // row, a shorter one leaves phase 2 more segments.  Phase 1 and 2 of 8000
+    // site configurations (1550 runs) 6.40 ms with 96, 6.43 with 64; of a
+    // coarse batch at 64^3 (some 350 runs) 3.26 ms with 96, 2.88 with 64,
+    // 2.62 by this rule; up to 96 runs all are tested here
+    const int k1 = nr <= CLASH_R1 ? nr : min(CLASH_R1, max(CLASH_CHORDS, nr / 12));
     const int NCH = min(nr, CLASH_CHORDS);
     // stride of the spread sample: near 0.618 of the runs after the chords.
     // Known defect: where it shares a factor with their number the walk misses
