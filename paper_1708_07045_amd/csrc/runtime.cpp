@@ -273,11 +273,11 @@ size_t csize() {
 }
 
 struct Plan {
-    // per configuration (plan order: batch order for a one-configuration
-    // plan, else grouped by z-window class; global_cfg is the batch index)
+    // the plan's configurations (all of the batch grouped by z-window class,
+    // or one alone; global_cfg is the batch index)
     std::vector<CfgDev> cfg;
     std::vector<int32_t> U;        // lattice coords, [sum atoms][3]
-    std::vector<int32_t> cfg_lig;  // ligand of each configuration
+    std::vector<int32_t> cfg_lig;  // ligand of each of them in batch order
     // chunks: contiguous ranges of the plan order
     struct Chunk {
         int c0, c1;               // plan positions [c0, c1)
@@ -347,12 +347,52 @@ double occ_threshold(const fftdg_grid_desc &g, double sigma) {
     return std::ceil(rho * rho * 4294967296.0);
 }
 
-// Place every configuration and build the chunked work lists.
-int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg, Plan &P) {
+// Whether place_one accepts each of a batch's configurations: first index it
+// refuses, or -1.  Rotated about its centroid a conformer spans at most twice
+// its radius, so only configurations near the limit or with a quaternion near
+// the ends of the number range are placed to find out.
+int first_unplaceable(const fftdg_batch *b, double h) {
+    size_t row = 0;
+    std::vector<double> radius;
+    std::vector<int32_t> U;
+    for (int l = 0; l < b->n_lig; ++l) {
+        const int na = b->atom_off[l + 1] - b->atom_off[l], nc = b->conf_off[l + 1] - b->conf_off[l];
+        const double *X0 = b->conf_xyz + 3 * row;
+        radius.assign(nc, 0.0);
+        for (int k = 0; k < nc; ++k) {
+            const double *X = X0 + 3 * (size_t)k * na;
+            double c[3] = {0, 0, 0}, r2 = 0.0;
+            for (int i = 0; i < 3 * na; ++i) c[i % 3] += X[i];
+            for (int d = 0; d < 3; ++d) c[d] /= na;
+            for (int i = 0; i < na; ++i) {
+                const double v[3] = {X[3 * i] - c[0], X[3 * i + 1] - c[1], X[3 * i + 2] - c[2]};
+                r2 = std::max(r2, v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+            }
+            radius[k] = std::sqrt(r2);
+        }
+        U.resize(3 * (size_t)na);
+        for (int c = b->cfg_off[l]; c < b->cfg_off[l + 1]; ++c) {
+            const double *q = b->cfg_quat + 4 * (size_t)c;
+            const double nq2 = q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3];
+            if (nq2 > 1e-200 && nq2 < 1e200 && 2.001 * radius[b->cfg_conf[c]] / h + 2.0 < 29000.0) continue;
+            int box[3];
+            if (!place_one(X0 + 3 * (size_t)b->cfg_conf[c] * na, na, q, h, U.data(), box)) return c;
+        }
+        row += (size_t)nc * na;
+    }
+    return -1;
+}
+
+// Place the configurations and build the chunked work lists: every one of the
+// batch, or (only_one) one_cfg alone, then P.cfg[0].  A batch with a
+// configuration that cannot be placed is refused either way; check_others
+// is false where an earlier call has looked.
+int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg, Plan &P, bool check_others = true) {
     const fftdg_grid_desc &g = ctx->g;
     const int N = g.n_fft, n_rec = g.n_rec;
     const bool occ = g.clash_mode == FFTDG_OCC;
-    const int ncfg = b->cfg_off[b->n_lig];
+    const int first = only_one ? one_cfg : 0;  // batch index of P.cfg[0] as placed
+    const int ncfg = only_one ? 1 : b->cfg_off[b->n_lig];
     P.cfg.assign(ncfg, CfgDev{});
     P.cfg_lig.assign(ncfg, 0);
     // atom / conformer-row offsets
@@ -365,8 +405,9 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
     std::vector<size_t> ubase(ncfg + 1, 0);
     for (int l = 0; l < b->n_lig; ++l)
         for (int c = b->cfg_off[l]; c < b->cfg_off[l + 1]; ++c) {
-            P.cfg_lig[c] = l;
-            ubase[c + 1] = b->atom_off[l + 1] - b->atom_off[l];
+            if (c < first || c >= first + ncfg) continue;
+            P.cfg_lig[c - first] = l;
+            ubase[c - first + 1] = b->atom_off[l + 1] - b->atom_off[l];
         }
     for (int c = 0; c < ncfg; ++c) ubase[c + 1] += ubase[c];
     P.U.assign(3 * ubase[ncfg], 0);
@@ -404,15 +445,21 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
             run_cap[l] = cap;
         }
     std::atomic<int> bad(-1), bad_geom(-1);
+    if (only_one && check_others) {
+        bad = first_unplaceable(b, g.h);
+        for (int l = 0; l < b->n_lig && occ; ++l)
+            for (int i = b->atom_off[l]; i < b->atom_off[l + 1]; ++i)
+                if (reach[i] >= 0 && 2 * reach[i] / 65536 + 2 >= N) bad_geom = b->cfg_off[l];
+    }
     auto work = [&](int c_begin, int c_end) {
-        for (int c = c_begin; c < c_end; ++c) {
-            const int l = P.cfg_lig[c];
+        for (int k = c_begin; k < c_end; ++k) {
+            const int l = P.cfg_lig[k], c = first + k;  // position, batch index
             const int na = b->atom_off[l + 1] - b->atom_off[l];
             const double *X = b->conf_xyz + 3 * (xyz_row[l] + (size_t)b->cfg_conf[c] * na);
-            int32_t *U = P.U.data() + 3 * ubase[c];
+            int32_t *U = P.U.data() + 3 * ubase[k];
             int box[3];
-            CfgDev &d = P.cfg[c];
-            d.u_base = (int32_t)ubase[c];
+            CfgDev &d = P.cfg[k];
+            d.u_base = (int32_t)ubase[k];
             d.atom_base = b->atom_off[l];
             d.n_atoms = na;
             d.global_cfg = c;
@@ -422,12 +469,12 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
                 continue;
             }
             long long nv = 1;
-            for (int k = 0; k < 3; ++k) {
-                d.V[k] = std::max(n_rec - box[k], 0);
-                nv *= d.V[k];
+            for (int e = 0; e < 3; ++e) {
+                d.V[e] = std::max(n_rec - box[e], 0);
+                nv *= d.V[e];
             }
             d.n_valid = (int32_t)nv;
-            const bool sel = (!only_one && (!b->cfg_select || b->cfg_select[c])) || (only_one && c == one_cfg);
+            const bool sel = only_one || !b->cfg_select || b->cfg_select[c];
             d.scanned = (sel && nv > 0) ? 1 : 0;
             // energy channel planes and rows (trilinear corners floor(u), floor(u)+1)
             int zlo = 1 << 30, zhi = -(1 << 30), ylo = 1 << 30, yhi = -(1 << 30);
@@ -554,7 +601,7 @@ int build_plan(fftdg_ctx *ctx, const fftdg_batch *b, bool only_one, int one_cfg,
                 d.occ_slot0 = 0;
                 d.pp_base = (int32_t)(ppt + pp);
                 d.run_off = (int32_t)nr;
-                d.run_cap = occ ? (int32_t)run_cap[P.cfg_lig[d.global_cfg]] : 0;
+                d.run_cap = occ ? (int32_t)run_cap[P.cfg_lig[d.global_cfg - first]] : 0;
                 d.free_off = (int32_t)nfw;
                 d.item_base = nit;
                 d.surv_off = (int32_t)nsv;
@@ -1365,13 +1412,9 @@ int fftdg_energy_grid(fftdg_ctx *ctx, int32_t snap, const fftdg_batch *b, int32_
     if (cfg < 0 || cfg >= ncfg) return set_err(ctx, FFTDG_E_INVALID, "energy_grid: configuration index out of range");
     if (!shape) return set_err(ctx, FFTDG_E_INVALID, "energy_grid: shape_host is NULL");
     if (!(T_K > 0.0) || !is_fin(T_K)) return set_err(ctx, FFTDG_E_INVALID, "energy_grid: temperature must be > 0");
-    // placement of this configuration only
-    const int l = (int)(std::upper_bound(b->cfg_off, b->cfg_off + b->n_lig + 1, cfg) - b->cfg_off) - 1;
-    fftdg_batch one = *b;
-    (void)l;
     Plan P;
-    if ((rc = build_plan(ctx, &one, true, cfg, P))) return rc;
-    const CfgDev &d = P.cfg[cfg];
+    if ((rc = build_plan(ctx, b, true, cfg, P))) return rc;
+    const CfgDev &d = P.cfg[0];
     shape[0] = d.V[2];
     shape[1] = d.V[1];
     shape[2] = d.V[0];
@@ -1829,8 +1872,8 @@ int fftdg_sample_poses(fftdg_ctx *ctx, const fftdg_batch *b, const fftdg_partial
         while (r < order.size() && pick[order[r]] == j) uu.push_back(u[2 * order[r++] + 1]);
         const int cfg = c0 + j;
         Plan PL;
-        if ((rc = build_plan(ctx, b, true, cfg, PL))) return rc;
-        const CfgDev &d = PL.cfg[cfg];
+        if ((rc = build_plan(ctx, b, true, cfg, PL, q == 0))) return rc;
+        const CfgDev &d = PL.cfg[0];
         const int n = d.n_valid;
         if (n <= 0) return set_err(ctx, FFTDG_E_INVALID, "sample_poses: drawn configuration has no valid translation");
         if ((rc = reserve(ctx, ctx->sir_psi, tsz * (size_t)n))) return rc;

@@ -43,3 +43,31 @@ def test_draws(n_rec, n_fft, atoms, mode, precision, r_ball):
         x = u[2 * k + 1] * cw[-1]
         want = min(int(np.searchsorted(cw, x, side="right")), int(np.flatnonzero(ok)[-1]))
         assert lin[k] == want or np.min(np.abs(cw - x)) <= 1e-10 * cw[-1], (k, lin[k], want)
+
+
+def test_one_configuration_of_a_batch():
+    """The grid of one configuration does not depend on the others of its
+    batch, and a batch with one that cannot be placed is refused whole."""
+    import copy
+    import paper_1708_07045_amd as fd
+    w = synth.tiny(seed=5, n_rec=24, n_fft=32, h=0.5, n_rec_atoms=6, n_lig_atoms=4, n_cfg=5, r_ball=1.5)
+    r = w.receptor
+    ctx = fd.FFTDG.from_workload(w)
+    g, o = ctx.receptor_grids(r.xyz[0], r.q, r.sigma, r.eps)
+    ctx.set_receptors(g[None].contiguous(), o[None].contiguous(), r.weights)
+    for c in (0, 3, 4):
+        alone = copy.deepcopy(w.ligands)
+        alone[0].cfg_conf, alone[0].cfg_quat = alone[0].cfg_conf[c:c + 1], alone[0].cfg_quat[c:c + 1]
+        a = ctx.energy_grid(0, fd.Batch(w.ligands), c, w.T)
+        b = ctx.energy_grid(0, fd.Batch(alone), 0, w.T)
+        assert a[0].numel() > 0 and all(bool((x == y).all()) for x, y in zip(a, b))
+    for k in range(3):
+        ligands = copy.deepcopy(w.ligands)
+        if k == 0:
+            ligands[0].cfg_quat[2] = 0.0
+        elif k == 1:
+            ligands[0].cfg_quat[2] = 1e-170
+        else:
+            ligands[0].conformers[ligands[0].cfg_conf[2]][0] += 1e5
+        with pytest.raises(fd.FFTDGError):
+            ctx.energy_grid(0, fd.Batch(ligands), 0, w.T)
