@@ -717,28 +717,31 @@ __global__ __launch_bounds__(NT) void k_grid_points(const T *__restrict__ grids,
     for (int ch = 0; ch < 3; ++ch) out[3 * i + ch] = grids[ch * n3 + i];
 }
 
-// Points x and x + 1 of a row: 6 values
-__device__ __forceinline__ void load_pair(__amdgpu_buffer_rsrc_t r, int vo, int so, float *v) {
-    const float4 a = buf_load4(r, vo, so);
-    const float2 b = buf_load(r, vo + 16, so, (float2 *)nullptr);
-    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y;
+// A grid point's three channels
+__device__ __forceinline__ void load_point(__amdgpu_buffer_rsrc_t r, int vo, int so, float *v) {
+    const u32x3 a = __builtin_amdgcn_raw_buffer_load_b96(r, vo, so, 0);
+    const uint32_t x = a.x, y = a.y, z = a.z;
+    v[0] = __builtin_bit_cast(float, x), v[1] = __builtin_bit_cast(float, y), v[2] = __builtin_bit_cast(float, z);
 }
-__device__ __forceinline__ void load_pair(__amdgpu_buffer_rsrc_t r, int vo, int so, double *v) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double2 a = buf_load(r, vo + 16 * k, so, (double2 *)nullptr);
-        v[2 * k] = a.x, v[2 * k + 1] = a.y;
-    }
+__device__ __forceinline__ void load_point(__amdgpu_buffer_rsrc_t r, int vo, int so, double *v) {
+    const double2 a = buf_load(r, vo, so, (double2 *)nullptr);
+    v[0] = a.x, v[1] = a.y;
+    v[2] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo + 16, so, 0));
 }
 
-// One block per (configuration, box-valid z-translation): the plane's free
-// translations, in order of their linear index, one per thread; a wavefront
-// walks the configuration's atoms, whose corners come as four times six
-// values (two points along x, three channels each) at the lane's translation
-// plus an offset in an SGPR, and whose 24 weights are scalar operands.
-// Bound: the loads' way through L1, 96 bytes per pair of translation and
-// atom, and the lines that feed it (with a grid per channel these were
-// twice as many: 8000 site configurations 6.9 -> 5.2 ms).
+// One block per (configuration, box-valid z-translation).  A lane has a point
+// of the plane that is a free translation or the point after one, in order of
+// the linear index.  A wavefront walks the configuration's atoms; a lane
+// reads the four grid points (two along y, two along z) at its own point plus
+// an offset in an SGPR, three channels each, and sums them with the atom's
+// weights for the near corners and with those for the far ones (scalar
+// operands).  The far sum belongs to the translation before, which is the
+// lane before: one shuffle after the last atom.  The last lane of a wavefront
+// only supplies that; its point is the first of the next group.
+// Bound: the loads' way through L1, 48 bytes a lane and atom.  8000 site
+// configurations (25 atoms, 96^3 in 128^3): 6.9 ms with both points of a pair
+// read by every lane and a grid per channel (lines twice as many), 5.2 with
+// the channels side by side, 3.4 with a point a lane.
 template <int N>
 __host__ __device__ constexpr int direct_threads() {
     return N == 128 ? 256 : 64;
@@ -754,7 +757,7 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
     constexpr int ND = direct_threads<N>(), NW = N / 32;
     constexpr int MAXW = N * NW;                   // words of a plane's free bits
     constexpr int PER = (MAXW + ND - 1) / ND;
-    __shared__ int pre[PER * ND + 1];              // free translations before each word
+    __shared__ int pre[PER * ND + 1];              // points read before each word
     __shared__ int sh[ND / 64];
     __shared__ LseAcc<T> red[ND / 64];
     const int ic = find_cfg(inv_off, n_cfg, (int)blockIdx.x);
@@ -779,14 +782,24 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
         }
         return;
     }
-    const int W = (Vx + 31) >> 5, nw = Vy * W;
-    const uint32_t *fp = fb + c.free_off + (int64_t)tz * nw;
+    const int W = (Vx + 31) >> 5, WS = (Vx >> 5) + 1, nw = Vy * WS;  // free words, slot words of a row
+    const uint32_t *fp = fb + c.free_off + (int64_t)tz * Vy * W;
+    // free bits of slot word w, and the points read: those and the ones after
+    auto free_word = [&](int w) {
+        const int r = w / WS, q = w - r * WS;
+        return q < W ? fp[r * W + q] : 0u;
+    };
+    auto slot_word = [&](int w) {
+        const int r = w / WS, q = w - r * WS;
+        const uint32_t f = q < W ? fp[r * W + q] : 0u;
+        return f | f << 1 | (q > 0 ? fp[r * W + q - 1] >> 31 : 0u);
+    };
     // running counts over the plane's words: thread t owns words PER t ..
     int cnt[PER], mine = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int w = PER * (int)threadIdx.x + k;
-        cnt[k] = w < nw ? __popc(fp[w]) : 0;
+        cnt[k] = w < nw ? __popc(slot_word(w)) : 0;
         mine += cnt[k];
     }
     int x = mine;
@@ -798,11 +811,11 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
     }
     if (lane == 63) sh[wv] = x;
     __syncthreads();
-    int base = x - mine, F = 0;
+    int base = x - mine, S = 0;
 #pragma unroll
     for (int i = 0; i < ND / 64; ++i) {
         base += i < wv ? sh[i] : 0;
-        F += sh[i];
+        S += sh[i];
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -813,34 +826,43 @@ __global__ __launch_bounds__(direct_threads<N>()) void k_direct(
     const int row = n_rec * 3 * (int)sizeof(T), plane = n_rec * row;
     const auto rs = make_rsrc(grids, n_rec * plane);
     const CornerAtom<T> *__restrict__ A = atoms + (int64_t)c.zrow * ma;
-    for (int j = threadIdx.x; j < F; j += ND) {
-        // word holding free translation j, then its (j - pre)-th set bit
-        int lo = 0, hi = nw;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= j) lo = mid; else hi = mid;
-        }
-        uint32_t b = fp[lo];
-        for (int k = j - pre[lo]; k > 0; --k) b &= b - 1u;
-        const int ty = lo / W, tx = 32 * (lo - (lo / W) * W) + __builtin_ctz(b);
-        const int vo = ((tz * n_rec + ty) * n_rec + tx) * 3 * (int)sizeof(T);
-        constexpr int UNR = sizeof(T) == 8 ? 1 : 2;  // atoms in flight: 89 and 68 registers
-        double sum = 0.0;  // over atoms in FP64: two instructions beside an atom's 24
-#pragma unroll UNR
-        for (int a = 0; a < n_atoms; ++a) {
-            const int off = A[a].off;
-            T e[2] = {(T)0, (T)0};
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                T v[6];
-                load_pair(rs, vo, off + (p >> 1) * plane + (p & 1) * row, v);
-#pragma unroll
-                for (int k = 0; k < 6; ++k) e[k / 3] += A[a].w[6 * p + k] * v[k];
+    for (int j0 = 63 * wv; j0 < S - 1; j0 += 63 * (ND / 64)) {  // the plane's last point is no translation
+        const int j = j0 + lane;
+        double near = 0.0, far = 0.0;  // over atoms in FP64: four instructions beside an atom's 24
+        int lin = -1;                  // of a free translation
+        if (j < S) {
+            // word holding slot j, then its (j - pre)-th set bit
+            int lo = 0, hi = nw;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (pre[mid] <= j) lo = mid; else hi = mid;
             }
-            sum += (double)(e[0] + e[1]);
+            uint32_t b = slot_word(lo);
+            for (int k = j - pre[lo]; k > 0; --k) b &= b - 1u;
+            const int bit = __builtin_ctz(b);
+            const int ty = lo / WS, tx = 32 * (lo - (lo / WS) * WS) + bit;
+            if (lane < 63 && (free_word(lo) >> bit & 1u)) lin = (tz * Vy + ty) * Vx + tx;
+            const int vo = ((tz * n_rec + ty) * n_rec + tx) * 3 * (int)sizeof(T);
+#pragma unroll 2
+            for (int a = 0; a < n_atoms; ++a) {
+                const int off = A[a].off;
+                T e[2] = {(T)0, (T)0};
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    T v[3];
+                    load_point(rs, vo, off + (p >> 1) * plane + (p & 1) * row, v);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) e[k / 3] += A[a].w[6 * p + k] * v[k % 3];
+                }
+                near += (double)e[0];
+                far += (double)e[1];
+            }
         }
-        const T psi = (T)sum;
-        acc.add(-beta * psi, psi, (tz * Vy + ty) * Vx + tx);
+        const double next = __shfl_down(far, 1);
+        if (lin >= 0) {
+            const T psi = (T)(near + next);
+            acc.add(-beta * psi, psi, lin);
+        }
     }
     block_partial_store<T, ND>(acc, red, pp + c.pp_base + tz);
 }
