@@ -618,15 +618,18 @@ __global__ void k_zero32(int32_t *__restrict__ p, int n) {
 // (free translation, atom) pairs of a configuration and snapshot, known on
 // the device once the clash test is done; a configuration with more than
 // direct_pairs goes through the transforms, listed by k_modes.  The lines lie
-// where the two cost the same (one stream, us per configuration): N = 128,
-// FP32: 5.5 ns per 1000 pairs (347 k pairs: 1.9 us) against 7.1-8.4 us of
-// transforms; N = 64: 12 ns per 1000 pairs against 1.15 us in FP32, 13 ns
-// against 2.3 us in FP64; N = 32: some 13 ns against 0.27 and 0.43 us.
-// 8000 site configurations (25 atoms, 3 % of the translations free, 160 k
-// pairs each): 46.0 ms of forward planes, z pass and inverse -> 5.2 ms.
+// a little below where the two cost the same (one stream, us per
+// configuration): N = 128, FP32: 0.2 + 2.7 per million pairs against 6.7-7.4
+// of transforms (8.1 at 347 k pairs and above), equal at 2.5 million; N = 64:
+// 0.12 + 3.6 against 1.0-1.15 in FP32, at 270 k, and 0.16 + 7.4 against 2.4 in
+// FP64, at 300 k; N = 32: 0.15 + 2.9 against 0.44, at 100 k, and 0.18 + 6.0
+// against 0.66, at 80 k (few ligands have as many there: the line is lower,
+// within 0.2 us of the better).  8000 site configurations (25 atoms, 3 % of the
+// translations free, 160 k pairs each): 46.0 ms of forward planes, z pass and
+// inverse -> 3.4 ms.
 template <typename T, int N>
 __host__ __device__ constexpr long long direct_pairs() {
-    return N == 128 ? 1000000 : (N == 64 ? (sizeof(T) == 8 ? 150000 : 100000) : (sizeof(T) == 8 ? 30000 : 20000));
+    return N == 128 ? 2000000 : (N == 64 ? (sizeof(T) == 8 ? 250000 : 200000) : 30000);
 }
 template <typename T, int N>
 __device__ __forceinline__ bool by_transforms(int n_free, int n_atoms) {
