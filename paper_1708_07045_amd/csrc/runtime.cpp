@@ -824,13 +824,21 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     // 10 snapshots of 24 ligands at 128^3 29 -> 27 ms
     const size_t set_bytes = sizeof(uint32_t) * (e_free + e_surv) + e_items;
     const size_t set_room = std::min<size_t>(std::min(ctx->ws_limit, (size_t)512 << 20) / set_bytes, 65535);  // grid.y
-    const int sgrp = P.fused && occ ? (int)std::max<size_t>(1, std::min<size_t>((size_t)(s_end - s_begin), set_room)) : 1;
+    int sgrp = P.fused && occ ? (int)std::max<size_t>(1, std::min<size_t>((size_t)(s_end - s_begin), set_room)) : 1;
     if (P.fused && occ) {
         if ((rc = reserve(ctx, ctx->runs, 2 * sizeof(uint32_t) * (size_t)std::max<int64_t>(P.max_runs, 1)))) return rc;
         if ((rc = reserve(ctx, ctx->run_cnt, sizeof(int32_t) * e_cfgs))) return rc;
-        if ((rc = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets * sgrp))) return rc;
-        if ((rc = reserve(ctx, ctx->lives, e_items * nsets * sgrp))) return rc;
-        if ((rc = reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets * sgrp))) return rc;
+        auto reserve_sets = [&]() {
+            int r = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets * sgrp);
+            if (!r) r = reserve(ctx, ctx->lives, e_items * nsets * sgrp);
+            return r ? r : reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets * sgrp);
+        };
+        rc = reserve_sets();
+        if (rc == FFTDG_E_NOMEM && sgrp > 1) {  // a full device: one snapshot at a time
+            sgrp = 1;
+            rc = reserve_sets();
+        }
+        if (rc) return rc;
     }
     // hybrid: energies summed directly at the clash-free translations where
     // they are few, through the transforms otherwise, decided on the device
