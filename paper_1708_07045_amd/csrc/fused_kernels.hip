@@ -631,6 +631,15 @@ template <typename T, int N>
 __host__ __device__ constexpr long long direct_pairs() {
     return N == 128 ? 2000000 : (N == 64 ? (sizeof(T) == 8 ? 250000 : 200000) : 30000);
 }
+// Configurations times snapshots of a scan from which the choice is offered:
+// its four launches cost some 20 us of a small scan's chain.  One scan with it
+// against without, us: N = 32, FP32, 256 configurations 212 : 192, 1000
+// 519 : 631; FP64, 16 92 : 89, 64 119 : 142; N = 64, FP32, 32 146 : 140, 64
+// 196 : 202; FP64, 4 105 : 102, 8 120 : 124; N = 128, 1 152 : 165.
+template <typename T, int N>
+constexpr int64_t direct_min() {
+    return N == 128 ? 1 : (N == 64 ? (sizeof(T) == 8 ? 8 : 48) : (sizeof(T) == 8 ? 32 : 400));
+}
 template <typename T, int N>
 __device__ __forceinline__ bool by_transforms(int n_free, int n_atoms) {
     return (long long)n_free * n_atoms > direct_pairs<T, N>();
@@ -1562,6 +1571,7 @@ static const FusedSet *make_fused() {
         LaunchFused<T, N>::lig_runs,
         LaunchFused<T, N>::zero,
         LaunchFused<T, N>::clash,
+        direct_min<T, N>(),
         sizeof(CornerAtom<T>),
         LaunchFused<T, N>::corner_atoms,
         LaunchFused<T, N>::modes,

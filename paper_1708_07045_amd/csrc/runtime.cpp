@@ -846,7 +846,8 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     // the whole scan: per chunk [done: nloc], then per item (chunk, snapshot)
     // [scnt: nloc][fcnt: nloc][out: 2] with nloc the chunk's configurations.
     const bool exporting = psi_out != nullptr || clash_out != nullptr;
-    const bool hybrid = P.fused && occ && !exporting;
+    const bool hybrid = P.fused && occ && !exporting &&
+                        (int64_t)P.zcfg.size() * (s_end - s_begin) >= ctx->fs->direct_min;
     int64_t n_counts = 0, nzmax = 1;
     std::vector<int64_t> count_off;  // of each chunk
     if (P.fused && occ) {
@@ -1107,7 +1108,7 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     const bool graph_ok = ctx->use_graph && !ctx->prof && !psi_out && !clash_out && out;
     if (!graph_ok) return launch_all(ctx->stream);
     std::vector<int64_t> sig = {(int64_t)(intptr_t)ks, occ, ctx->edirect, grp, s_begin, s_end, P.fused, P.fused_planes,
-                                overlap, (int64_t)(intptr_t)ctx->side, sgrp,
+                                overlap, (int64_t)(intptr_t)ctx->side, sgrp, hybrid,
                                 (int64_t)(intptr_t)ctx->runs.p, (int64_t)(intptr_t)ctx->run_cnt.p,
                                 (int64_t)(intptr_t)ctx->fbits.p, (int64_t)(intptr_t)ctx->lives.p,
                                 (int64_t)(intptr_t)ctx->dil.p, (int64_t)o_item, (int64_t)(intptr_t)ctx->zat.p,

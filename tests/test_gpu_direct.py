@@ -30,6 +30,11 @@ def _workload(n_fft, n_rec, h, precision, sizes, seed):
 # to over 256 free translations, rows of one to four words
 CASES = [(32, 30, 0.5, "f32", [(1, 2), (6, 3)]), (64, 48, 0.5, "f32", [(1, 3), (3, 2), (10, 2)]),
          (64, 48, 0.5, "f64", [(3, 1), (8, 2)]), (128, 100, 0.25, "f32", [(1, 1), (3, 2), (14, 2)])]
+# enough configurations for the choice to be offered on the small grids; one
+# atom or eight and more (at most 32 or at least 97 runs: the clash test's known
+# defect, held by its own test, is between)
+CASES += [(32, 30, 0.5, "f32", [(1, 140), (8, 60)]), (32, 30, 0.5, "f64", [(1, 10), (8, 6)]),
+          (64, 48, 0.5, "f32", [(1, 14), (10, 10)]), (64, 48, 0.5, "f64", [(1, 1), (8, 3)])]
 
 
 @pytest.mark.parametrize("n_fft,n_rec,h,precision,sizes", CASES)
