@@ -232,9 +232,12 @@ int fftdg_reduce_static(fftdg_ctx *ctx, const fftdg_batch *b, const fftdg_partia
 
 /* Kernel timing with HIP events recorded on the context's stream around
  * every launch the library makes (for benchmarks).  Kernel ids:
- *   0 ligand xy forward   1 z-pencil product   2 inverse xy + log-sum-exp
+ *   0 ligand xy forward   1 z-pencil product
+ *   2 inverse xy + log-sum-exp, and the energies summed directly (fused path)
  *   3 plane merge         4 receptor spectra   5 FP64 reduce
- *   6 ligand occupancy runs (fused path)       7 clash test on bits (fused path)
+ *   6 ligand occupancy runs and the direct sums' atom tables (fused path)
+ *   7 clash test on bits and the choice between direct sums and transforms
+ *     (fused path)
  * fftdg_profile(ctx, 1) clears the counters and starts recording; 0 stops.
  * fftdg_profile_read synchronizes the stream and returns, for kernel id k,
  * the summed event time (ms), the launch count and the algorithmic HBM
@@ -342,8 +345,10 @@ int fftdg_pair_energies(int device, void *hip_stream, int32_t n_rec_atoms, const
  *                      128): only the three energy channels go through the
  *                      FFT; in OCC mode the clash test of Eq. 10 is made
  *                      exactly on bits (ligand occupancy runs against
- *                      OR-dilated receptor occupancy rows) before the z pass,
- *                      and only z-translations with a clash-free translation
+ *                      OR-dilated receptor occupancy rows) first; where few
+ *                      translations of a configuration are clash-free its
+ *                      energies are summed directly at those alone, else
+ *                      only z-translations with a clash-free translation
  *                      are stored and inverse-transformed.  1: the energy
  *                      planes' x/y transforms come from the direct per-atom
  *                      forward pass through device memory; 2: the z-pencil
@@ -356,8 +361,8 @@ int fftdg_pair_energies(int device, void *hip_stream, int32_t n_rec_atoms, const
  *                      (default priority, created on first use), its
  *                      buffers double-buffered and the streams ordered by
  *                      events: on the fused path in OCC mode the clash test
- *                      of the next (chunk, snapshot) runs on it beside the z
- *                      pass and inverse of the current one; on the plane
+ *                      of the next chunk and group of snapshots runs on it
+ *                      beside the energies of the current one; on the plane
  *                      path (fused = 0) the inverse xy of one z pass runs on
  *                      it beside the next z pass (twice the inverse
  *                      workspace).  0 runs everything on the context's
