@@ -1,5 +1,6 @@
-// Fused scan path for gfx950 (wave64): energy channels only through the FFT,
-// clashes by an exact bitwise test.
+// Fused scan path for gfx950 (wave64): clashes by an exact bitwise test, then
+// energies summed at the clash-free translations where these are few (k_direct),
+// else the energy channels alone through the FFT.
 //
 // Clash test (occupancy mode, Eq. 10).  The overlap count of Eq. 10 is
 // positive exactly when some occupied ligand grid point n lands on an
@@ -14,7 +15,7 @@
 //   - a run of length L starting at x = a meets receptor occupancy at
 //     translation t iff D_k(a + t_x) | D_k(a + L - 2^k + t_x) on row
 //     (y + t_y, z + t_z), 2^k <= L < 2^(k+1); one 32-bit word answers 32
-//     x-translations at once (k_clash).
+//     x-translations at once (k_clash1, k_clash2).
 // The result is the clash mask the FFT threshold reproduces, without its
 // rounding: every decision is an integer one.
 //

@@ -289,7 +289,7 @@ struct Plan {
         int zhalf;                // 1: every scanned configuration's energy planes lie in [0, n_fft/2); 2: and some occupancy window is longer than n_fft/2
         // fused path
         int nitems;               // clash-test items (tz, 64-row group)
-        int nitems2;              // phase-2 items (64-row slices of the undecided-row lists)
+        int nitems2;              // phase-2 blocks (each takes every n-th 64 undecided segments)
         int64_t nsurv;            // undecided-segment list slots
         int64_t nruns, nfree;     // run slots, free-bit words
         int max_atoms;            // most atoms of a scanned configuration
@@ -805,9 +805,9 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
         if ((rc = reserve(ctx, ctx->zat, ctx->fs->zat_bytes * (size_t)max_nz_atoms))) return rc;
         if ((rc = reserve(ctx, ctx->zbt, sizeof(int32_t) * (size_t)nzmax * (g.n_fft + 2)))) return rc;
     }
-    // second stream.  Fused path, OCC: the clash test of the next (chunk,
-    // snapshot) item runs on the side stream beside the z pass and inverse of
-    // the current one; its results (free bits, live flags, undecided-row
+    // second stream.  Fused path, OCC: the clash test of the next item, a chunk
+    // and a group of snapshots, runs on the side stream beside the energies of
+    // the current one; its results (free bits, live flags, undecided-segment
     // lists) alternate between two buffer sets.  Plane path: the inverse xy
     // of one z pass runs on the side stream beside the next z pass; the
     // inverse planes alternate between two workspace sets.
