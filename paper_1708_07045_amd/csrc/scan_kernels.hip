@@ -2085,6 +2085,7 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
         hit[k] = 0;
     }
     const double k6 = pow(2.0, -1.0 / 6.0);
+    const double span = fabs(ox) + fabs(oy) + fabs(oz) + h * n_rec;  // no grid coordinate is larger
     for (int a0 = 0; a0 < n_atoms; a0 += NS) {
         __syncthreads();
         const int a = a0 + threadIdx.x;
@@ -2092,11 +2093,15 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
             const double s3 = sg[a] * sg[a] * sg[a], se = sqrt(ep[a]), rex = k6 * sg[a];
             const double r2 = root_threshold(rex), o2 = root_threshold(occ_f * rex);
             const double ele = 332.05 * q[a], ljr = se * s3 * s3, lja = se * s3;
-            // pairs at or past near2 need no test; numerators that are not finite
-            // must not meet the zero of an excluded pair: always tested
-            const bool fin = isfinite(ele) && isfinite(ljr) && isfinite(lja);
+            // pairs at or past near2 need no test.  Always tested: numerators that
+            // are not finite, which must not meet the zero of an excluded pair, and
+            // atoms so far off that a squared distance may overflow (they add
+            // nothing, where inverse_root of infinity is no number).  No distance is
+            // at or past a near2 of NaN
+            const bool fin = isfinite(ele) && isfinite(ljr) && isfinite(lja) &&
+                             fabs(xyz[3 * a]) + fabs(xyz[3 * a + 1]) + fabs(xyz[3 * a + 2]) + span < 1e150;
             at[threadIdx.x] = Atom{xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], ele, ljr, lja, r2, o2,
-                                   fin ? fmax(fmax(r2, o2), 1e-30) : INFINITY, 0.0};
+                                   fin ? fmax(fmax(r2, o2), 1e-30) : NAN, 0.0};
         }
         __syncthreads();
         const int na = min(NS, n_atoms - a0);
@@ -2151,8 +2156,8 @@ __global__ __launch_bounds__(RG_NT * RG_S) void k_receptor_grids(int n_atoms, co
                     }
                     continue;
                 }
-                // a point on the atom (or nowhere), or a numerator that is not
-                // finite and must not meet a zero: the plain quotients
+                // a point on the atom (or nowhere), an atom at no finite distance, or
+                // a numerator that is not finite: the plain quotients
 #pragma unroll 1
                 for (int k = 0; k < RG_P; ++k) quotients(A, k);
                 continue;
