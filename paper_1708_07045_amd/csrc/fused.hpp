@@ -109,7 +109,8 @@ struct FusedSet {
                         const int32_t *ulat, const void *gam, void *zat, int32_t *zbt);
     size_t zat_bytes;  // bytes of one atom record
     // z pass of one snapshot (spectra rspec, 3 energy channels); with clash,
-    // of the configurations zlist[0 .. nfft[0]) (indices into zcfg)
+    // only the z-translations whose live flag is set, and with a zlist only
+    // the configurations zlist[0 .. nfft[0]) (indices into zcfg)
     hipError_t (*zpass)(hipStream_t, bool zhalf, bool clash, const CfgDev *cfgs, const int32_t *zcfg, int nz,
                         int max_atoms, const void *zat, const int32_t *zbt, const void *rspec, const void *tw,
                         void *wsi, const uint8_t *live, const int32_t *zlist, const int32_t *nfft);

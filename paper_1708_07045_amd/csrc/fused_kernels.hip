@@ -939,16 +939,16 @@ __global__ __launch_bounds__(NT) void k_zprep(const CfgDev *__restrict__ cfgs, c
 
 // Block -> (tile of P z-pencils, configuration), with the XCD-aware order
 // of the plane path's z kernel: block b of a launch of nb takes logical index
-// (b mod 8) (nb / 8) + b / 8.  LIST: the configurations are those of zlist,
-// nfft[0] of them, a count the host does not know; a grid of fixed size
-// then strides over the same order (a launch that finds no configuration
+// (b mod 8) (nb / 8) + b / 8.  LIST and a zlist: the configurations are those
+// of zlist, nfft[0] of them, a count the host does not know; a grid of fixed
+// size then strides over the same order (a launch that finds no configuration
 // ends after one load a block).
 template <bool LIST>
 struct ZWork {
     int nz, total, nb, b;
     const int32_t *zlist;
     __device__ ZWork(int n, int n_tiles, const int32_t *list, const int32_t *nfft) {
-        nz = LIST ? nfft[0] : n;
+        nz = LIST && list ? nfft[0] : n;
         total = n_tiles * nz;
         nb = LIST ? (total + 7) & ~7 : (int)gridDim.x;
         b = (int)blockIdx.x;
@@ -961,7 +961,7 @@ struct ZWork {
         if (L >= total) return false;
         tile = L / nz;
         zi = L - tile * nz;
-        if (LIST) zi = zlist[zi];
+        if (LIST && zlist) zi = zlist[zi];
         return true;
     }
 };
@@ -1513,7 +1513,7 @@ struct LaunchFused {
                             void *wsi, const uint8_t *live, const int32_t *zlist, const int32_t *nfft) {
         if (nz <= 0) return hipSuccess;
         const int n_tiles = (G::NP + G::U - 1) / G::U;
-        const long long nb = z_blocks(n_tiles, nz, clash);
+        const long long nb = z_blocks(n_tiles, nz, zlist != nullptr);
         const int ac = max_atoms < atoms_per_table() ? max_atoms : atoms_per_table();
         const size_t dyn = dyn_bytes(max_atoms);
 #define FFTDG_ZF(Z, C)                                                                                            \
@@ -1532,7 +1532,7 @@ struct LaunchFused {
                               const uint8_t *live, const int32_t *zlist, const int32_t *nfft) {
         if (nz <= 0) return hipSuccess;
         const int n_tiles = (G::NP + G::U - 1) / G::U;
-        const long long nb = z_blocks(n_tiles, nz, clash);
+        const long long nb = z_blocks(n_tiles, nz, zlist != nullptr);
 #define FFTDG_ZP(Z, C)                                                                                     \
     hipLaunchKernelGGL((k_zplanes<T, N, Z, C>), dim3((unsigned)nb), dim3(NT), 0, st, cfgs, zcfg, nz, n_tiles, \
                        (const C2 *)ws, (const C2 *)rspec, (const C2 *)tw, (C2 *)wsi, live, zlist, nfft)

@@ -1010,9 +1010,9 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
                 const double b_z = hybrid ? 0.0 : b_spec3 + (P.fused_planes ? (double)ch.ws_fwd * cb : 0.0);
                 HIPCHK(ctx, timed(ctx, FFTDG_K_ZPROD, b_z, [&] {
                            if (P.fused_planes)
-                               return fs->zplanes(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                               return fs->zplanes(st, ch.zhalf != 0, occ && !exporting, ccfg, dz + ch.z0, (int)ch.nz,
                                                   ctx->ws_fwd.p, rs, ctx->tw.p, ctx->ws_inv.p, lv_of(p, k), zl, md);
-                           return fs->zpass(st, ch.zhalf != 0, hybrid, ccfg, dz + ch.z0, (int)ch.nz,
+                           return fs->zpass(st, ch.zhalf != 0, occ && !exporting, ccfg, dz + ch.z0, (int)ch.nz,
                                             std::max(ch.max_atoms, 1), ctx->zat.p, (const int32_t *)ctx->zbt.p, rs,
                                             ctx->tw.p, ctx->ws_inv.p, lv_of(p, k), zl, md);
                        }));

@@ -1,0 +1,93 @@
+"""What the host runtime allocates and launches, without a GPU: libfftdg.so over a stand-in of the HIP calls
+(hip_host.cpp), which notes the kernels' names and gives device memory of a set size.  Each test is a
+process of its own, so nothing else sees the stand-in."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+DRIVER = '''
+import ctypes, re, sys
+import numpy as np
+host = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+host.host_capacity.argtypes = [ctypes.c_size_t]
+host.host_in_use.restype = ctypes.c_size_t
+host.host_launches.restype = ctypes.c_char_p
+import paper_1708_07045_amd as fd
+from paper_1708_07045_amd import _lib as lib
+from workload import synth
+L = fd.load()
+NO_LIMIT = 2 ** 64 - 1
+OUT = ctypes.c_void_p(4096)  # never read: kernels do nothing
+
+
+def create(n_fft, n_rec, precision="f32", mode="occ", h=0.5):
+    g = lib.GridDesc(n_rec, n_fft, h, (ctypes.c_double * 3)(0, 0, 0), lib.F64 if precision == "f64" else lib.F32,
+                     lib.OCC if mode == "occ" else lib.CAP, 10.0, 0.5)
+    c = ctypes.c_void_p()
+    assert L.fftdg_create(ctypes.byref(c), ctypes.byref(g), 0, None) == lib.OK
+    return c
+
+
+def receptors(c, n):
+    return L.fftdg_set_receptors(c, n, OUT, OUT, None)
+
+
+def ligand(n_cfg, n_at=6):
+    rs = synth.streams(5)
+    return synth.make_ligand(rs[1], rs[2], n_at, 1, n_cfg)
+
+
+def kernels():
+    """(name, integer and bool template arguments) of the launches since the last call"""
+    t = host.host_launches().decode().split()
+    host.host_clear()
+    parts = [re.match(r"_ZN5fftdg(\\d+)(.*)", n) for n in t]
+    return [(m[2][:int(m[1])], re.findall(r"L[ib](\\d+)E", m[2])) for m in parts]
+
+
+def scan(c, b):
+    """(status, kernels launched)"""
+    kernels()
+    return L.fftdg_scan(c, ctypes.byref(b.c), 300.0, OUT), kernels()
+
+'''
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "hip_host.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-o", so, os.path.join(HERE, "hip_host.cpp"), "-ldl"])
+    return so
+
+
+def drive(stand_in, body):
+    r = subprocess.run([sys.executable, "-c", DRIVER + body, stand_in], cwd=os.path.dirname(HERE), capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+@pytest.mark.parametrize("precision,n_fft,n_rec", [("f32", 32, 30), ("f64", 32, 30), ("f32", 64, 48), ("f32", 128, 96)])
+def test_only_live_planes_are_transformed(stand_in, precision, n_fft, n_rec):
+    """A scan in occupancy mode runs the form of the z pass that skips z-translations without a clash-free one
+    (last template argument), however few configurations it has; an export runs the other form."""
+    drive(stand_in, f'''
+c = create({n_fft}, {n_rec}, "{precision}")
+assert receptors(c, 2) == lib.OK
+shape = np.zeros(3, np.int32)
+for fused in (1, 2):
+    t = lib.Tuning(256, 0, 1, 0, fused, 1)
+    assert L.fftdg_set_tuning(c, ctypes.byref(t)) == lib.OK
+    for n in (1, 700):
+        b = fd.Batch([ligand(n)])
+        rc, ks = scan(c, b)
+        z = [a for k, a in ks if k in ("k_zplanes", "k_zfused")]
+        assert rc == lib.OK and z and all(a[-1] == "1" for a in z), (n, z)
+    assert L.fftdg_energy_grid(c, 0, ctypes.byref(b.c), 0, 300.0, OUT, OUT, shape.ctypes.data) == lib.OK
+    z = [a for k, a in kernels() if k in ("k_zplanes", "k_zfused")]
+    assert z and all(a[-1] == "0" for a in z), z
+''')
