@@ -785,7 +785,7 @@ def main():
     # it is the kernels' loads through L1.
     scan_med = float(np.median(scan_ms))
     scans = n_cfg * n_snap
-    direct = fused and w.clash_mode == "occ"
+    direct = fused and w.clash_mode == "occ" and w.n_fft >= 64
     path_bytes = sum(prof[k][2] for k in ("lig_fwd_xy", "zprod", "inv_xy_lse", "merge", "lig_runs", "clash")
                      if k in prof) / n_prof
     scan_bytes = path_bytes if direct else pb * scans

@@ -347,9 +347,13 @@ int fftdg_pair_energies(int device, void *hip_stream, int32_t n_rec_atoms, const
  *                      exactly on bits (ligand occupancy runs against
  *                      OR-dilated receptor occupancy rows) first; where few
  *                      translations of a configuration are clash-free its
- *                      energies are summed directly at those alone, else
- *                      only z-translations with a clash-free translation
- *                      are stored and inverse-transformed.  1: the energy
+ *                      energies are summed directly at those alone (n_fft 64
+ *                      and 128; a rule on the configuration's own counts, so
+ *                      its record does not depend on what else a call
+ *                      scans), else only z-translations with a clash-free
+ *                      translation are stored and inverse-transformed.  The
+ *                      energies of fftdg_energy_grid are the transforms', so
+ *                      a record agrees with them to rounding.  1: the energy
  *                      planes' x/y transforms come from the direct per-atom
  *                      forward pass through device memory; 2: the z-pencil
  *                      kernel forms its inputs itself from the per-atom

@@ -82,10 +82,8 @@ struct FusedSet {
                         int n_cfg, int n_items, int n_items2, const CfgDev *cfgs, const uint32_t *runs,
                         const int32_t *run_count, const uint32_t *dil, uint32_t *fb, uint8_t *live, uint32_t *surv,
                         int32_t *scnt, int32_t *fcnt);
-    // configurations times snapshots of a scan from which choosing between
-    // direct sums and transforms pays its four launches
-    int64_t direct_min;
-    // direct energies: per scanned configuration its atoms' corner offsets
+    // direct energies (direct and what belongs to it are nullptr where every
+    // configuration takes the transforms, see offers_direct): per scanned configuration its atoms' corner offsets
     // and weights (nz x max_atoms records of corner_bytes); which
     // configurations go through the transforms (zlist, need, out[2] as
     // k_modes writes them; done: one int per configuration, zero at the

@@ -614,8 +614,8 @@ __global__ void k_zero32(int32_t *__restrict__ p, int n) {
 // Eq. 8 with the trilinear weights written out: at translation t,
 //   Psi(t) = sum_a sum_(8 corners) w sum_ch gamma_ch G_ch(floor(u_a) + t + corner),
 // the sum the transforms evaluate at every translation.  Where few
-// translations are clash-free it is evaluated at those alone (k_direct): no
-// forward planes, no z pass, no inverse.  What decides is the number of
+// translations are clash-free it is evaluated at those alone (k_direct; N = 64
+// and 128): no forward planes, no z pass, no inverse.  What decides is the number of
 // (free translation, atom) pairs of a configuration and snapshot, known on
 // the device once the clash test is done; a configuration with more than
 // direct_pairs goes through the transforms, listed by k_modes.  The lines lie
@@ -623,23 +623,25 @@ __global__ void k_zero32(int32_t *__restrict__ p, int n) {
 // configuration): N = 128, FP32: 0.2 + 2.7 per million pairs against 6.7-7.4
 // of transforms (8.1 at 347 k pairs and above), equal at 2.5 million; N = 64:
 // 0.12 + 3.6 against 1.0-1.15 in FP32, at 270 k, and 0.16 + 7.4 against 2.4 in
-// FP64, at 300 k; N = 32: 0.15 + 2.9 against 0.44, at 100 k, and 0.18 + 6.0
-// against 0.66, at 80 k (few ligands have as many there: the line is lower,
-// within 0.2 us of the better).  8000 site configurations (25 atoms, 3 % of the
+// FP64, at 300 k.  8000 site configurations (25 atoms, 3 % of the
 // translations free, 160 k pairs each): 46.0 ms of forward planes, z pass and
 // inverse -> 3.4 ms.
 template <typename T, int N>
 __host__ __device__ constexpr long long direct_pairs() {
-    return N == 128 ? 2000000 : (N == 64 ? (sizeof(T) == 8 ? 250000 : 200000) : 30000);
+    return N == 128 ? 2000000 : (sizeof(T) == 8 ? 250000 : 200000);
 }
-// Configurations times snapshots of a scan from which the choice is offered:
-// its four launches cost some 20 us of a small scan's chain.  One scan with it
-// against without, us: N = 32, FP32, 256 configurations 212 : 192, 1000
-// 519 : 631; FP64, 16 92 : 89, 64 119 : 142; N = 64, FP32, 32 146 : 140, 64
-// 196 : 202; FP64, 4 105 : 102, 8 120 : 124; N = 128, 1 152 : 165.
-template <typename T, int N>
-constexpr int64_t direct_min() {
-    return N == 128 ? 1 : (N == 64 ? (sizeof(T) == 8 ? 8 : 48) : (sizeof(T) == 8 ? 32 : 400));
+// Whether a grid offers the choice.  It goes by the grid alone: a
+// configuration's record is then the same, to the last bit, whatever others
+// its call scans.  At N = 32 a transform is so short that the choice's launches,
+// some 20 us of a scan's chain, cost as much as it saves: one scan and reduce
+// with it against without, us: FP64, 1 configuration 169 : 122, 31 190 : 148,
+// 1000 706-765 : 672-787; FP32, 1 188 : 151, 1000 760 : 610-700, 4000
+// 1590-1770 : 1420-1730 (300 receptor atoms).  At N = 64 it costs a scan of one
+// configuration less than 20 us and pays from a few on: FP32, 1 173 : 158, 24
+// 203 : 208, 47 220-228 : 227; FP64, 1 156 : 129, 4 170-176 : 173, 7 168-176 : 179.
+template <int N>
+constexpr bool offers_direct() {
+    return N >= 64;
 }
 template <typename T, int N>
 __device__ __forceinline__ bool by_transforms(int n_free, int n_atoms) {
@@ -1554,8 +1556,12 @@ struct LaunchFused {
     hipLaunchKernelGGL((k_inv_fused<T, N, C, L>), dim3(nb), dim3(inv_fused_threads<N>()), 0, st, inv_off, n_cfg, cfgs, \
                        (const C2 *)wsi, b, s, (const C2 *)tw, fb, live, (PlanePartial<T> *)pp, (T *)psi_out,        \
                        clash_out, e_count, n_items, fcnt, nfft)
-        if (clash && fcnt) FFTDG_INV(true, true);
-        else if (clash) FFTDG_INV(true, false);
+        if constexpr (offers_direct<N>())
+            if (clash && fcnt) {
+                FFTDG_INV(true, true);
+                return hipGetLastError();
+            }
+        if (clash) FFTDG_INV(true, false);
         else FFTDG_INV(false, false);
 #undef FFTDG_INV
         return hipGetLastError();
@@ -1563,28 +1569,34 @@ struct LaunchFused {
 };
 
 template <typename T, int N>
+static FusedSet fused_launchers() {
+    using L = LaunchFused<T, N>;
+    FusedSet s{};
+    s.n_fft = N;
+    s.dil_words = Dil<N>::words();
+    s.margin = Dil<N>::M;
+    s.rec_dilate = L::rec_dilate;
+    s.lig_runs = L::lig_runs;
+    s.zero = L::zero;
+    s.clash = L::clash;
+    if constexpr (offers_direct<N>()) {
+        s.corner_bytes = sizeof(CornerAtom<T>);
+        s.corner_atoms = L::corner_atoms;
+        s.modes = L::modes;
+        s.direct = L::direct;
+        s.grid_points = L::grid_points;
+    }
+    s.zprep = L::zprep;
+    s.zat_bytes = sizeof(ZAtom<T>);
+    s.zpass = L::zpass;
+    s.zplanes = L::zplanes;
+    s.inv = L::inv;
+    s.z_lds = L::dyn_bytes;
+    return s;
+}
+template <typename T, int N>
 static const FusedSet *make_fused() {
-    static const FusedSet s = {
-        N,
-        Dil<N>::words(),
-        Dil<N>::M,
-        LaunchFused<T, N>::rec_dilate,
-        LaunchFused<T, N>::lig_runs,
-        LaunchFused<T, N>::zero,
-        LaunchFused<T, N>::clash,
-        direct_min<T, N>(),
-        sizeof(CornerAtom<T>),
-        LaunchFused<T, N>::corner_atoms,
-        LaunchFused<T, N>::modes,
-        LaunchFused<T, N>::direct,
-        LaunchFused<T, N>::grid_points,
-        LaunchFused<T, N>::zprep,
-        sizeof(ZAtom<T>),
-        LaunchFused<T, N>::zpass,
-        LaunchFused<T, N>::zplanes,
-        LaunchFused<T, N>::inv,
-        LaunchFused<T, N>::dyn_bytes,
-    };
+    static const FusedSet s = fused_launchers<T, N>();
     return &s;
 }
 

@@ -23,7 +23,7 @@ struct KernelSet {
     hipError_t (*fwd)(hipStream_t, bool edf, const int32_t *fwd_off, int n_cfg, int n_items, const CfgDev *cfgs,
                       const int32_t *ulat, const void *gam, const double *thr, const void *tw, void *ws);
     // the energy planes (direct form, three channels an item) of the
-    // configurations marked in need, nneed[0] of them (nullptr at N = 256)
+    // configurations marked in need, nneed[0] of them (nullptr at N = 32 and 256)
     hipError_t (*fwd_need)(hipStream_t, const int32_t *fwd_off, int n_cfg, int n_items, const CfgDev *cfgs,
                            const int32_t *ulat, const void *gam, const void *tw, void *ws, const uint8_t *need,
                            const int32_t *nneed);

@@ -842,12 +842,12 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     }
     // hybrid: energies summed directly at the clash-free translations where
     // they are few, through the transforms otherwise, decided on the device
-    // per configuration and snapshot.  Its counts start at zero, one clear for
+    // per configuration and snapshot, and by what the context is, never by what
+    // else a call scans.  The counts start at zero, one clear for
     // the whole scan: per chunk [done: nloc], then per item (chunk, snapshot)
     // [scnt: nloc][fcnt: nloc][out: 2] with nloc the chunk's configurations.
     const bool exporting = psi_out != nullptr || clash_out != nullptr;
-    const bool hybrid = P.fused && occ && !exporting &&
-                        (int64_t)P.zcfg.size() * (s_end - s_begin) >= ctx->fs->direct_min;
+    const bool hybrid = P.fused && occ && !exporting && ctx->fs->direct;
     int64_t n_counts = 0, nzmax = 1;
     std::vector<int64_t> count_off;  // of each chunk
     if (P.fused && occ) {
@@ -1387,8 +1387,8 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
                        return ctx->fs->rec_dilate(ctx->stream, occ + s * n3, g.n_rec, (uint32_t *)ctx->dil.p + s * dw);
                    }));
         // the grids themselves, for the energies summed directly
-        if ((rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
-        for (int s = 0; s < n_snap; ++s)
+        if (ctx->fs->direct && (rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
+        for (int s = 0; s < n_snap && ctx->fs->direct; ++s)
             HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, 6.0 * (double)(n3 * tsz), [&] {
                        return ctx->fs->grid_points(ctx->stream, (const char *)grids + s * 3 * n3 * tsz, g.n_rec,
                                                    (char *)ctx->rgrid.p + s * 3 * n3 * tsz);

@@ -2371,6 +2371,8 @@ static const KernelSet *make_split_set() {
 
 template <typename T, int N>
 static const KernelSet *make_set() {
+    decltype(KernelSet::fwd_need) fwd_need = nullptr;
+    if constexpr (N >= 64) fwd_need = Launch<T, N>::fwd_need;
     static const KernelSet s = {
         N,
         (int)sizeof(typename Cx<T>::t),
@@ -2378,7 +2380,7 @@ static const KernelSet *make_set() {
         Geo<T, N>::NP,
         Launch<T, N>::rec_spectra,
         Launch<T, N>::fwd,
-        Launch<T, N>::fwd_need,
+        fwd_need,
         Launch<T, N>::zprod,
         Launch<T, N>::inv,
         Launch<T, N>::merge,

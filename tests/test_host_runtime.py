@@ -91,3 +91,21 @@ for fused in (1, 2):
     z = [a for k, a in kernels() if k in ("k_zplanes", "k_zfused")]
     assert z and all(a[-1] == "0" for a in z), z
 ''')
+
+
+@pytest.mark.parametrize("precision,n_fft,n_rec", [("f32", 32, 30), ("f64", 32, 30), ("f32", 64, 48), ("f64", 64, 48),
+                                                   ("f32", 128, 96)])
+def test_way_of_the_energies_goes_by_the_grid(stand_in, precision, n_fft, n_rec):
+    """Which kernels form the energies does not depend on how many configurations a scan has."""
+    drive(stand_in, f'''
+c = create({n_fft}, {n_rec}, "{precision}")
+for snaps in (1, 3):
+    assert receptors(c, snaps) == lib.OK
+    used = []
+    for n in (1, 700):
+        rc, ks = scan(c, fd.Batch([ligand(n)]))
+        assert rc == lib.OK
+        used.append({{k for k, _ in ks}})
+    assert used[0] == used[1], used[0] ^ used[1]
+    assert ("k_direct" in used[0]) == ({n_fft} >= 64)
+''')
