@@ -163,7 +163,10 @@ int fftdg_receptor_grids(fftdg_ctx *ctx, int32_t n_atoms, const double *xyz_dev,
  *   w_host    [n_snap] snapshot weights W of Eq. 13 (normalised internally,
  *             must be >= 0 with a positive sum); NULL = uniform.
  * The library owns the spectra; the caller may free its grids once the
- * stream has passed this call.  Replaces any previous receptor set. */
+ * stream has passed this call.  Replaces any previous receptor set; a call
+ * that fails past its argument checks (E_NOMEM, E_DEVICE) leaves the context
+ * without one (E_STATE from the calls that need it; partials of the previous
+ * set can still be reduced). */
 int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids_dev,
                         const uint8_t *occ_dev, const double *w_host);
 

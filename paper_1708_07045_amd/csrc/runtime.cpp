@@ -97,6 +97,7 @@ struct fftdg_ctx {
     DevBuf sir_psi, sir_clash, sir_u, sir_lin, sir_psi_out, sir_seg;  // pose resampling
     int n_snap = 0;
     std::vector<double> W;
+    bool receptors = false;  // the device buffers hold those n_snap snapshots
     void *pinned = nullptr;
     size_t pinned_n = 0;
     hipEvent_t staging_ev = nullptr;
@@ -1363,11 +1364,19 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
     const fftdg_grid_desc &g = ctx->g;
     const size_t cb = ctx->ks->cbytes;
     const size_t per_snap = (size_t)ctx->n_ch * g.n_fft * ctx->ks->np * cb;
+    const size_t n3 = (size_t)g.n_rec * g.n_rec * g.n_rec;
+    const size_t tsz = g.precision == FFTDG_F32 ? 4 : 8;
+    const bool bits = is_occ && ctx->fs, sums = bits && ctx->fs->direct;  // the fused path's own forms of a snapshot
+    const size_t dw = bits ? (size_t)ctx->fs->dil_words : 0;
+    // the previous set ends here: a call that fails from here on leaves the
+    // context without receptors to scan (n_snap and W stay those of the
+    // partials that a caller may still reduce)
+    ctx->receptors = false;
     int rc;
     if ((rc = reserve(ctx, ctx->rspec, per_snap * n_snap))) return rc;
     if ((rc = reserve(ctx, ctx->rxy, (size_t)ctx->n_ch * g.n_rec * ctx->ks->np * cb))) return rc;
-    const size_t n3 = (size_t)g.n_rec * g.n_rec * g.n_rec;
-    const size_t tsz = g.precision == FFTDG_F32 ? 4 : 8;
+    if (bits && (rc = reserve(ctx, ctx->dil, sizeof(uint32_t) * dw * n_snap))) return rc;
+    if (sums && (rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
     // bytes: grids read, xy planes written and read back, spectra written
     const double b_spec = (double)(3 * n3 * tsz + (is_occ ? n3 : 0)) +
                           2.0 * ctx->n_ch * g.n_rec * (double)ctx->ks->np * cb + (double)per_snap;
@@ -1378,30 +1387,26 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
                                                ctx->rxy.p, (char *)ctx->rspec.p + s * per_snap);
                }));
     }
-    if (is_occ && ctx->fs) {
-        // bit rows of the clash test (fused path), one table per snapshot
-        const size_t dw = (size_t)ctx->fs->dil_words;
-        if ((rc = reserve(ctx, ctx->dil, sizeof(uint32_t) * dw * n_snap))) return rc;
-        for (int s = 0; s < n_snap; ++s)
-            HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, (double)n3 + 4.0 * (double)dw, [&] {
-                       return ctx->fs->rec_dilate(ctx->stream, occ + s * n3, g.n_rec, (uint32_t *)ctx->dil.p + s * dw);
-                   }));
-        // the grids themselves, for the energies summed directly
-        if (ctx->fs->direct && (rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
-        for (int s = 0; s < n_snap && ctx->fs->direct; ++s)
-            HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, 6.0 * (double)(n3 * tsz), [&] {
-                       return ctx->fs->grid_points(ctx->stream, (const char *)grids + s * 3 * n3 * tsz, g.n_rec,
-                                                   (char *)ctx->rgrid.p + s * 3 * n3 * tsz);
-                   }));
-    }
+    // bit rows of the clash test, one table per snapshot
+    for (int s = 0; bits && s < n_snap; ++s)
+        HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, (double)n3 + 4.0 * (double)dw, [&] {
+                   return ctx->fs->rec_dilate(ctx->stream, occ + s * n3, g.n_rec, (uint32_t *)ctx->dil.p + s * dw);
+               }));
+    // the grids themselves, for the energies summed directly
+    for (int s = 0; sums && s < n_snap; ++s)
+        HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, 6.0 * (double)(n3 * tsz), [&] {
+                   return ctx->fs->grid_points(ctx->stream, (const char *)grids + s * 3 * n3 * tsz, g.n_rec,
+                                               (char *)ctx->rgrid.p + s * 3 * n3 * tsz);
+               }));
     ctx->n_snap = n_snap;
     ctx->W = W;
+    ctx->receptors = true;
     return FFTDG_OK;
 }
 
 int fftdg_scan(fftdg_ctx *ctx, const fftdg_batch *b, double T_K, fftdg_partial *out) {
     if (!ctx) return FFTDG_E_INVALID;
-    if (ctx->n_snap <= 0) return set_err(ctx, FFTDG_E_STATE, "scan before set_receptors");
+    if (!ctx->receptors) return set_err(ctx, FFTDG_E_STATE, "scan before set_receptors");
     if (!out) return set_err(ctx, FFTDG_E_INVALID, "scan: out_dev is NULL");
     if (!(T_K > 0.0) || !is_fin(T_K)) return set_err(ctx, FFTDG_E_INVALID, "scan: temperature must be finite and > 0");
     int rc = validate_batch(ctx, b);
@@ -1428,7 +1433,7 @@ int fftdg_energy_grid(fftdg_ctx *ctx, int32_t snap, const fftdg_batch *b, int32_
     shape[1] = d.V[1];
     shape[2] = d.V[0];
     if (!psi) return FFTDG_OK;
-    if (ctx->n_snap <= 0) return set_err(ctx, FFTDG_E_STATE, "energy_grid before set_receptors");
+    if (!ctx->receptors) return set_err(ctx, FFTDG_E_STATE, "energy_grid before set_receptors");
     if (snap < 0 || snap >= ctx->n_snap) return set_err(ctx, FFTDG_E_INVALID, "energy_grid: snapshot out of range");
     if (d.n_valid <= 0) return FFTDG_OK;
     HIPCHK(ctx, hipSetDevice(ctx->device));
@@ -1630,7 +1635,7 @@ int fftdg_config_features(fftdg_ctx *ctx, const fftdg_batch *b, float *feat) {
 int fftdg_autotune(fftdg_ctx *ctx, const fftdg_batch *b, double T_K, int32_t max_cfgs, fftdg_tuning *out,
                    double *ms_host) {
     if (!ctx) return FFTDG_E_INVALID;
-    if (ctx->n_snap <= 0) return set_err(ctx, FFTDG_E_STATE, "autotune before set_receptors");
+    if (!ctx->receptors) return set_err(ctx, FFTDG_E_STATE, "autotune before set_receptors");
     if (max_cfgs < 1) return set_err(ctx, FFTDG_E_INVALID, "autotune: max_cfgs must be >= 1");
     if (!(T_K > 0.0) || !is_fin(T_K)) return set_err(ctx, FFTDG_E_INVALID, "autotune: temperature must be > 0");
     int rc = validate_batch(ctx, b);
@@ -1828,7 +1833,7 @@ int fftdg_is_plan(fftdg_ctx *ctx, const fftdg_batch *b, const float *yhat, doubl
 int fftdg_sample_poses(fftdg_ctx *ctx, const fftdg_batch *b, const fftdg_partial *p, int32_t lig, int32_t snap,
                        double T_K, int32_t K, const double *u, int32_t *cfg_out, int32_t *t_out, double *psi_out) {
     if (!ctx) return FFTDG_E_INVALID;
-    if (ctx->n_snap <= 0) return set_err(ctx, FFTDG_E_STATE, "sample_poses before set_receptors");
+    if (!ctx->receptors) return set_err(ctx, FFTDG_E_STATE, "sample_poses before set_receptors");
     int rc = validate_batch(ctx, b);
     if (rc) return rc;
     if (lig < 0 || lig >= b->n_lig) return set_err(ctx, FFTDG_E_INVALID, "sample_poses: ligand out of range");

@@ -109,3 +109,39 @@ for snaps in (1, 3):
     assert used[0] == used[1], used[0] ^ used[1]
     assert ("k_direct" in used[0]) == ({n_fft} >= 64)
 ''')
+
+
+@pytest.mark.parametrize("mode,n_fft,n_rec", [("occ", 32, 30), ("occ", 64, 48), ("cap", 64, 48), ("occ", 256, 200)])
+def test_receptors_that_do_not_fit_leave_none(stand_in, mode, n_fft, n_rec):
+    """Whichever allocation of set_receptors fails, the context then has no receptors: nothing is launched over the
+    buffers that the call gave up, and the next set is taken as the first was."""
+    drive(stand_in, f'''
+b = fd.Batch([ligand(3)])
+c = create({n_fft}, {n_rec}, mode="{mode}")
+failed = set()
+for part in np.linspace(0, 1, 60):
+    host.host_capacity(NO_LIMIT)
+    assert receptors(c, 2) == lib.OK
+    assert scan(c, b)[0] == lib.OK
+    base = host.host_in_use()
+    if not failed:
+        assert receptors(c, 40) == lib.OK
+        full = host.host_in_use()
+        L.fftdg_destroy(c)
+        c = create({n_fft}, {n_rec}, mode="{mode}")
+        assert receptors(c, 2) == lib.OK and scan(c, b)[0] == lib.OK
+    host.host_capacity(int(base + part * (full - base) * 0.98))
+    rc = receptors(c, 40)
+    failed.add(rc)
+    host.host_capacity(NO_LIMIT)
+    if rc != lib.OK:
+        assert rc == lib.E_NOMEM
+        assert scan(c, b) == (lib.E_STATE, [])
+        res, B = np.zeros(1, lib.RESULT_DTYPE), np.zeros((1, 2))
+        assert L.fftdg_reduce(c, ctypes.byref(b.c), OUT, None, 300.0, B.ctypes.data, res.ctypes.data) == lib.OK
+        shape = np.zeros(3, np.int32)
+        assert L.fftdg_energy_grid(c, 0, ctypes.byref(b.c), 0, 300.0, OUT, OUT, shape.ctypes.data) == lib.E_STATE
+    L.fftdg_destroy(c)
+    c = create({n_fft}, {n_rec}, mode="{mode}")
+assert lib.E_NOMEM in failed
+''')
