@@ -166,7 +166,10 @@ int fftdg_receptor_grids(fftdg_ctx *ctx, int32_t n_atoms, const double *xyz_dev,
  * stream has passed this call.  Replaces any previous receptor set; a call
  * that fails past its argument checks (E_NOMEM, E_DEVICE) leaves the context
  * without one (E_STATE from the calls that need it; partials of the previous
- * set can still be reduced). */
+ * set can still be reduced).  Beside the spectra the context keeps the clash
+ * test's tables and, for the energies summed directly, a copy of the grids;
+ * where a device is too full for that copy scans do without it, by the
+ * transforms alone. */
 int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids_dev,
                         const uint8_t *occ_dev, const double *w_host);
 

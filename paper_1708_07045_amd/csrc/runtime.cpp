@@ -98,6 +98,7 @@ struct fftdg_ctx {
     int n_snap = 0;
     std::vector<double> W;
     bool receptors = false;  // the device buffers hold those n_snap snapshots
+    bool grouped = true;     // several snapshots a launch (false once a set's buffers for them did not fit)
     void *pinned = nullptr;
     size_t pinned_n = 0;
     hipEvent_t staging_ev = nullptr;
@@ -177,17 +178,31 @@ hipError_t timed(fftdg_ctx *c, int k, double bytes, F &&fn) {
     return e;
 }
 
-int reserve(fftdg_ctx *c, DevBuf &b, size_t bytes) {
+// Gives a buffer back once the work of the context's stream is done.
+int release(fftdg_ctx *c, DevBuf &b) {
+    if (!b.p) return FFTDG_OK;
+    hipError_t e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return set_err(c, FFTDG_E_DEVICE, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
+    (void)hipFree(b.p);
+    b.p = nullptr;
+    b.n = 0;
+    return FFTDG_OK;
+}
+
+// At least `bytes` in b.  On a full device the copy of the receptor grids goes
+// first (scans then take the transforms), unless keep_grids.
+int reserve(fftdg_ctx *c, DevBuf &b, size_t bytes, bool keep_grids = false) {
     if (bytes <= b.n) return FFTDG_OK;
-    if (b.p) {
-        hipError_t e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return set_err(c, FFTDG_E_DEVICE, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
-        (void)hipFree(b.p);
-        b.p = nullptr;
-        b.n = 0;
-    }
+    int rc = release(c, b);
+    if (rc) return rc;
     size_t want = bytes + bytes / 8 + 256;
     hipError_t e = hipMalloc(&b.p, want);
+    if (e != hipSuccess) b.p = nullptr;
+    if (e != hipSuccess && !keep_grids && c->rgrid.p) {
+        (void)hipGetLastError();
+        if ((rc = release(c, c->rgrid))) return rc;
+        e = hipMalloc(&b.p, want);
+    }
     if (e != hipSuccess) {
         b.p = nullptr;
         (void)hipGetLastError();
@@ -794,17 +809,10 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     double *thr = (double *)(h + o_thr);
     for (int i = 0; i < na; ++i) thr[i] = occ ? occ_threshold(g, b->sigma[i]) : 0.0;
     const size_t cb = (size_t)ctx->ks->cbytes;
-    if ((!P.fused || P.fused_planes) && (rc = reserve(ctx, ctx->ws_fwd, cb * (size_t)std::max<int64_t>(P.max_fwd, 1))))
-        return rc;
-    int64_t max_nz_atoms = 1;
-    if (P.fused) {
-        int64_t nzmax = 1;
-        for (const Plan::Chunk &ch : P.chunks) {
-            nzmax = std::max<int64_t>(nzmax, (int64_t)ch.nz);
-            max_nz_atoms = std::max<int64_t>(max_nz_atoms, (int64_t)ch.nz * std::max(ch.max_atoms, 1));
-        }
-        if ((rc = reserve(ctx, ctx->zat, ctx->fs->zat_bytes * (size_t)max_nz_atoms))) return rc;
-        if ((rc = reserve(ctx, ctx->zbt, sizeof(int32_t) * (size_t)nzmax * (g.n_fft + 2)))) return rc;
+    int64_t max_nz_atoms = 1, nzmax = 1;
+    for (const Plan::Chunk &ch : P.chunks) {
+        nzmax = std::max<int64_t>(nzmax, (int64_t)ch.nz);
+        max_nz_atoms = std::max<int64_t>(max_nz_atoms, (int64_t)ch.nz * std::max(ch.max_atoms, 1));
     }
     // second stream.  Fused path, OCC: the clash test of the next item, a chunk
     // and a group of snapshots, runs on the side stream beside the energies of
@@ -819,52 +827,32 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
     const int s_begin = snap_only >= 0 ? snap_only : 0;
     const int s_end = snap_only >= 0 ? snap_only + 1 : ctx->n_snap;
     // snapshots of one launch of the clash test and the direct energies: as
-    // many as keep a buffer set under half a GiB and the workspace limit.  One
-    // snapshot of a chunk does not fill the chip on a coarse grid, and each
-    // launch costs its gap: 24 chunks of 5 snapshots at 64^3 12.0 -> 8.3 ms,
-    // 10 snapshots of 24 ligands at 128^3 29 -> 27 ms
+    // many as keep a buffer set under half a GiB.  One snapshot of a chunk does
+    // not fill the chip on a coarse grid, and each launch costs its gap: 24
+    // chunks of 5 snapshots at 64^3 12.0 -> 8.3 ms, 10 snapshots of 24 ligands
+    // at 128^3 29 -> 27 ms
     const size_t set_bytes = sizeof(uint32_t) * (e_free + e_surv) + e_items;
-    const size_t set_room = std::min<size_t>(std::min(ctx->ws_limit, (size_t)512 << 20) / set_bytes, 65535);  // grid.y
-    int sgrp = P.fused && occ ? (int)std::max<size_t>(1, std::min<size_t>((size_t)(s_end - s_begin), set_room)) : 1;
-    if (P.fused && occ) {
-        if ((rc = reserve(ctx, ctx->runs, 2 * sizeof(uint32_t) * (size_t)std::max<int64_t>(P.max_runs, 1)))) return rc;
-        if ((rc = reserve(ctx, ctx->run_cnt, sizeof(int32_t) * e_cfgs))) return rc;
-        auto reserve_sets = [&]() {
-            int r = reserve(ctx, ctx->fbits, sizeof(uint32_t) * e_free * nsets * sgrp);
-            if (!r) r = reserve(ctx, ctx->lives, e_items * nsets * sgrp);
-            return r ? r : reserve(ctx, ctx->surv, sizeof(uint32_t) * e_surv * nsets * sgrp);
-        };
-        rc = reserve_sets();
-        if (rc == FFTDG_E_NOMEM && sgrp > 1) {  // a full device: one snapshot at a time
-            sgrp = 1;
-            rc = reserve_sets();
-        }
-        if (rc) return rc;
-    }
+    const size_t set_room = std::min<size_t>(((size_t)512 << 20) / set_bytes, 65535);  // grid.y
+    int sgrp = P.fused && occ && ctx->grouped
+                   ? (int)std::max<size_t>(1, std::min<size_t>((size_t)(s_end - s_begin), set_room))
+                   : 1;
     // hybrid: energies summed directly at the clash-free translations where
     // they are few, through the transforms otherwise, decided on the device
     // per configuration and snapshot, and by what the context is, never by what
-    // else a call scans.  The counts start at zero, one clear for
-    // the whole scan: per chunk [done: nloc], then per item (chunk, snapshot)
-    // [scnt: nloc][fcnt: nloc][out: 2] with nloc the chunk's configurations.
+    // else a call scans.  The counts start at zero, one clear for the whole
+    // scan: per chunk [done: nloc], then per item (chunk, snapshot) [scnt: nloc]
+    // [fcnt: nloc][out: 2] with nloc the chunk's configurations.
     const bool exporting = psi_out != nullptr || clash_out != nullptr;
-    const bool hybrid = P.fused && occ && !exporting && ctx->fs->direct;
-    int64_t n_counts = 0, nzmax = 1;
+    bool hybrid = P.fused && occ && !exporting && ctx->fs->direct && ctx->rgrid.p;
+    int64_t n_counts = 0;
     std::vector<int64_t> count_off;  // of each chunk
     if (P.fused && occ) {
         for (const Plan::Chunk &ch : P.chunks) {
             const int64_t nloc = ch.c1 - ch.c0;
             count_off.push_back(n_counts);
             n_counts += nloc + (int64_t)(s_end - s_begin) * (2 * nloc + 2);
-            nzmax = std::max<int64_t>(nzmax, (int64_t)ch.nz);
         }
         if (n_counts > INT32_MAX) return set_err(ctx, FFTDG_E_INVALID, "scan: more than 2^31 clash-test counters in one batch");
-        if ((rc = reserve(ctx, ctx->counts, sizeof(int32_t) * (size_t)n_counts))) return rc;
-    }
-    if (hybrid) {
-        if ((rc = reserve(ctx, ctx->corners, ctx->fs->corner_bytes * (size_t)max_nz_atoms))) return rc;
-        if ((rc = reserve(ctx, ctx->zlist, sizeof(int32_t) * (size_t)nzmax * nsets * sgrp))) return rc;
-        if ((rc = reserve(ctx, ctx->need, e_cfgs * nsets))) return rc;
     }
     if (overlap && !ctx->side) {
         // the events first: the stream is set only once all of them exist,
@@ -884,11 +872,51 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
                             : (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(s_end - s_begin), room / inv1,
                                                                            (int64_t)ctx->snap_group}));
     const size_t inv_set = cb * (size_t)inv1 * grp;  // bytes of one workspace set of inverse planes
-    if ((rc = reserve(ctx, ctx->ws_inv, inv_set * (overlap && !P.fused ? 2 : 1)))) return rc;
     // plane partials of the whole scan, one region per snapshot, merged into
     // configuration partials once per snapshot after the last chunk
     const size_t pp_snap = (size_t)ctx->ks->ppbytes * (size_t)std::max<int64_t>(P.total_pp, 1);
-    if ((rc = reserve(ctx, ctx->pp, pp_snap * (size_t)(s_end - s_begin)))) return rc;
+    // Device memory.  On a full device a scan goes on with less: one snapshot
+    // at a time, then without the copy of the grids and so by the transforms
+    // alone; what it no longer needs is given back before each further attempt.
+    auto reserve_all = [&]() -> int {
+        int r = FFTDG_OK;
+        auto need = [&](DevBuf &b, size_t bytes) {
+            if (!r) r = reserve(ctx, b, bytes, true);
+        };
+        if (!P.fused || P.fused_planes) need(ctx->ws_fwd, cb * (size_t)std::max<int64_t>(P.max_fwd, 1));
+        need(ctx->ws_inv, inv_set * (overlap && !P.fused ? 2 : 1));
+        need(ctx->pp, pp_snap * (size_t)(s_end - s_begin));
+        if (P.fused) {
+            need(ctx->zat, ctx->fs->zat_bytes * (size_t)max_nz_atoms);
+            need(ctx->zbt, sizeof(int32_t) * (size_t)nzmax * (g.n_fft + 2));
+        }
+        if (P.fused && occ) {
+            need(ctx->runs, 2 * sizeof(uint32_t) * (size_t)std::max<int64_t>(P.max_runs, 1));
+            need(ctx->run_cnt, sizeof(int32_t) * e_cfgs);
+            need(ctx->counts, sizeof(int32_t) * (size_t)n_counts);
+            need(ctx->fbits, sizeof(uint32_t) * e_free * nsets * sgrp);
+            need(ctx->lives, e_items * nsets * sgrp);
+            need(ctx->surv, sizeof(uint32_t) * e_surv * nsets * sgrp);
+        }
+        if (hybrid) {
+            need(ctx->corners, ctx->fs->corner_bytes * (size_t)max_nz_atoms);
+            need(ctx->zlist, sizeof(int32_t) * (size_t)nzmax * nsets * sgrp);
+            need(ctx->need, e_cfgs * nsets);
+        }
+        return r;
+    };
+    while ((rc = reserve_all()) == FFTDG_E_NOMEM && (sgrp > 1 || ctx->rgrid.p)) {
+        const bool group = sgrp > 1;
+        sgrp = 1;
+        ctx->grouped = false;
+        for (DevBuf *b : {&ctx->fbits, &ctx->lives, &ctx->surv, &ctx->zlist})
+            if ((rc = release(ctx, *b))) return rc;
+        if (group) continue;
+        hybrid = false;
+        for (DevBuf *b : {&ctx->rgrid, &ctx->corners, &ctx->need})
+            if ((rc = release(ctx, *b))) return rc;
+    }
+    if (rc) return rc;
     HIPCHK(ctx, hipMemcpyAsync(ctx->tables.p, h, total, hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(ctx, hipEventRecord(ctx->staging_ev, ctx->stream));
     ctx->staging_used = true;
@@ -1366,17 +1394,19 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
     const size_t per_snap = (size_t)ctx->n_ch * g.n_fft * ctx->ks->np * cb;
     const size_t n3 = (size_t)g.n_rec * g.n_rec * g.n_rec;
     const size_t tsz = g.precision == FFTDG_F32 ? 4 : 8;
-    const bool bits = is_occ && ctx->fs, sums = bits && ctx->fs->direct;  // the fused path's own forms of a snapshot
+    const bool bits = is_occ && ctx->fs, sums = bits && ctx->fs->direct;  // fused path: clash table, grids by point
     const size_t dw = bits ? (size_t)ctx->fs->dil_words : 0;
     // the previous set ends here: a call that fails from here on leaves the
     // context without receptors to scan (n_snap and W stay those of the
     // partials that a caller may still reduce)
     ctx->receptors = false;
+    ctx->grouped = true;
     int rc;
     if ((rc = reserve(ctx, ctx->rspec, per_snap * n_snap))) return rc;
     if ((rc = reserve(ctx, ctx->rxy, (size_t)ctx->n_ch * g.n_rec * ctx->ks->np * cb))) return rc;
     if (bits && (rc = reserve(ctx, ctx->dil, sizeof(uint32_t) * dw * n_snap))) return rc;
-    if (sums && (rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap))) return rc;
+    // the copy of the grids is for speed: where it does not fit, scans take the transforms
+    if (sums && (rc = reserve(ctx, ctx->rgrid, 3 * n3 * tsz * n_snap)) && rc != FFTDG_E_NOMEM) return rc;
     // bytes: grids read, xy planes written and read back, spectra written
     const double b_spec = (double)(3 * n3 * tsz + (is_occ ? n3 : 0)) +
                           2.0 * ctx->n_ch * g.n_rec * (double)ctx->ks->np * cb + (double)per_snap;
@@ -1393,7 +1423,7 @@ int fftdg_set_receptors(fftdg_ctx *ctx, int32_t n_snap, const void *grids, const
                    return ctx->fs->rec_dilate(ctx->stream, occ + s * n3, g.n_rec, (uint32_t *)ctx->dil.p + s * dw);
                }));
     // the grids themselves, for the energies summed directly
-    for (int s = 0; sums && s < n_snap; ++s)
+    for (int s = 0; ctx->rgrid.p && s < n_snap; ++s)
         HIPCHK(ctx, timed(ctx, FFTDG_K_SPECTRA, 6.0 * (double)(n3 * tsz), [&] {
                    return ctx->fs->grid_points(ctx->stream, (const char *)grids + s * 3 * n3 * tsz, g.n_rec,
                                                (char *)ctx->rgrid.p + s * 3 * n3 * tsz);

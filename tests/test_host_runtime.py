@@ -145,3 +145,45 @@ for part in np.linspace(0, 1, 60):
     c = create({n_fft}, {n_rec}, mode="{mode}")
 assert lib.E_NOMEM in failed
 ''')
+
+
+@pytest.mark.parametrize("n_fft,n_rec,snaps", [(64, 48, 6), (128, 96, 3)])
+def test_scan_on_a_full_device_goes_on_with_less(stand_in, n_fft, n_rec, snaps):
+    """As the memory shrinks a scan gives up the launches over several snapshots, then the copy of the grids (and
+    takes the transforms, over live planes), and only then says that it does not fit: at what it needed without
+    either.  Draws from it fit where it does."""
+    drive(stand_in, f'''
+b = fd.Batch([ligand(40)])
+grids = {snaps} * 3 * {n_rec} ** 3 * 4
+
+
+def attempt(capacity):
+    """(statuses of set_receptors, scan and an export, kernels of the scan, bytes in use)"""
+    host.host_capacity(NO_LIMIT)
+    c = create({n_fft}, {n_rec})
+    base = host.host_in_use()
+    host.host_capacity(capacity + base if capacity < NO_LIMIT else capacity)
+    rc = [receptors(c, {snaps})]
+    s, ks = scan(c, b)
+    shape = np.zeros(3, np.int32)
+    rc += [s, L.fftdg_energy_grid(c, 0, ctypes.byref(b.c), 0, 300.0, OUT, OUT, shape.ctypes.data)]
+    used = host.host_in_use() - base
+    L.fftdg_destroy(c)
+    return rc, [k for k, _ in ks], [a for k, a in ks if k in ("k_zplanes", "k_zfused")], used
+
+
+rc, ks, _, full = attempt(NO_LIMIT)
+assert rc == [lib.OK] * 3 and ks.count("k_direct") == 1
+seen, least = set(), full
+for capacity in np.linspace(full, 0.3 * full, 400).astype(int).tolist():
+    rc, ks, z, used = attempt(capacity)
+    assert used <= capacity
+    if rc != [lib.OK] * 3:
+        assert set(rc) <= {{lib.OK, lib.E_NOMEM, lib.E_STATE}}
+        break
+    least = capacity
+    assert ks.count("k_direct") in (0, 1, {snaps}) and all(a[-1] == "1" for a in z)
+    seen.add(ks.count("k_direct"))
+assert seen == {{0, 1, {snaps}}}, seen
+assert least < full - 1.1 * grids
+''')
