@@ -1440,8 +1440,11 @@ struct LaunchFused {
         return hipGetLastError();
     }
     static hipError_t zero(hipStream_t st, int32_t *p, int64_t n) {
-        if (n <= 0) return hipSuccess;
-        hipLaunchKernelGGL(k_zero32, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, st, p, (int)n);
+        constexpr int64_t most = 1 << 30;  // of a launch, whose threads must number fewer than 2^32
+        for (; n > 0; p += most, n -= most) {
+            const int k = (int)(n < most ? n : most);
+            hipLaunchKernelGGL(k_zero32, dim3((unsigned)((k + NT - 1) / NT)), dim3(NT), 0, st, p, k);
+        }
         return hipGetLastError();
     }
     static hipError_t clash(hipStream_t st, int ns, const SnapStride &ss, const int32_t *item_off,

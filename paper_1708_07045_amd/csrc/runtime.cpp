@@ -852,7 +852,6 @@ int run_plan(fftdg_ctx *ctx, const fftdg_batch *b, const Plan &P, double T_K, ff
             count_off.push_back(n_counts);
             n_counts += nloc + (int64_t)(s_end - s_begin) * (2 * nloc + 2);
         }
-        if (n_counts > INT32_MAX) return set_err(ctx, FFTDG_E_INVALID, "scan: more than 2^31 clash-test counters in one batch");
     }
     if (overlap && !ctx->side) {
         // the events first: the stream is set only once all of them exist,

@@ -187,3 +187,18 @@ for capacity in np.linspace(full, 0.3 * full, 400).astype(int).tolist():
 assert seen == {{0, 1, {snaps}}}, seen
 assert least < full - 1.1 * grids
 ''')
+
+
+def test_counters_beyond_two_to_the_31(stand_in):
+    """One configuration in 600 000 scanned against 2000 snapshots: the clash test's counters number 2.4e9."""
+    drive(stand_in, '''
+n = 600_000
+sel = np.zeros(n, np.uint8)
+sel[7] = 1
+b = fd.Batch([ligand(n, 1)]).with_select(sel)
+c = create(32, 20)
+assert receptors(c, 2000) == lib.OK
+rc, ks = scan(c, b)
+assert rc == lib.OK, L.fftdg_last_error(c)
+assert [k for k, _ in ks].count("k_zero32") == 3
+''')
