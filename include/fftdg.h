@@ -359,7 +359,10 @@ int fftdg_pair_energies(int device, void *hip_stream, int32_t n_rec_atoms, const
  *                      scans), else only z-translations with a clash-free
  *                      translation are stored and inverse-transformed.  The
  *                      energies of fftdg_energy_grid are the transforms', so
- *                      a record agrees with them to rounding.  1: the energy
+ *                      a record agrees with them to rounding.  Known defect:
+ *                      configurations of 33 to 96 occupancy runs (ligands of
+ *                      a few atoms on a coarse grid) can keep translations
+ *                      that clash; fused = 0 does not have it.  1: the energy
  *                      planes' x/y transforms come from the direct per-atom
  *                      forward pass through device memory; 2: the z-pencil
  *                      kernel forms its inputs itself from the per-atom

@@ -17,7 +17,8 @@
 //     (y + t_y, z + t_z), 2^k <= L < 2^(k+1); one 32-bit word answers 32
 //     x-translations at once (k_clash1, k_clash2).
 // The result is the clash mask the FFT threshold reproduces, without its
-// rounding: every decision is an integer one.
+// rounding: every decision is an integer one.  (Known defect: configurations of
+// 33 to 96 runs can keep clashing translations, see k_clash1's stride.)
 //
 // Energy channels (Eqs. 4-9).  The x/y DFT of a trilinearly spread atom
 // factorises,
@@ -461,10 +462,11 @@ __global__ __launch_bounds__(NT) void k_clash1(const int32_t *__restrict__ item_
     const int k1 = nr <= CLASH_R1 ? nr : min(CLASH_R1, max(CLASH_CHORDS, nr / 12));
     const int NCH = min(nr, CLASH_CHORDS);
     // stride of the spread sample: near 0.618 of the runs after the chords.
-    // Known defect: where it shares a factor with their number the walk misses
-    // some, and with nr <= CLASH_R1 the row counts as decided all the same
-    // (ligands of a few atoms on a coarse grid keep clashing translations);
-    // a stride of 1 there mends it and changes those ligands' results
+    // Known defect: where it shares a factor with their number R the walk visits
+    // R / gcd of them, and with nr <= CLASH_R1 the row counts as decided all the
+    // same: 24 of the 64 counts nr = 33 .. 96 (ligands of a few atoms on a coarse
+    // grid) keep clashing translations.  A stride of 1 where nr <= CLASH_R1 mends
+    // it and changes those ligands' results
     const int S = max(1, (nr - NCH) * 618 / 1000) % max(1, nr - NCH);
     const auto rsrc = make_rsrc(dil, (int)(D::words() * 4));
     clash_dispatch<N>(W, reinterpret_cast<const uint2 *>(runs) + c.run_off, nr, k1, NCH, S, tz, ty, act, lm, rsrc, acc);
